@@ -227,6 +227,13 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  *     P V products.  The second waits for the first with a bounded wait
  *     (about 0.1 s); past it that split's partial is NaN, so out shows it;
  *   - 64-token tiles of K and V rows otherwise.
+ * Before these, in automatic mode with out != NULL and no kv_debug: calls with
+ * bf16, head_dim 256, at most 16 query heads, d_model >= 1024 and B *
+ * n_kv_heads * ceil(T_rec / 64) >= 192 recompute keys only.  Values enter
+ * attention as sum_t p_t V_t = W_v sum_t p_t hbar_t, so the residuals are read a
+ * second time, weighted with the probabilities, and W_v is applied once (three
+ * kernels; scores from unrounded keys).  Their scratch lies in the same
+ * workspace, and they use the completion words as arrival counters.
  * With bf16, T_rec >= 1 and T_tail <= 4 (a decode step's current token) the
  * tail joins the last tile's split on every engine: its rows are copied into
  * LDS while that tile is recomputed.  Otherwise the tail adds one split per

@@ -507,12 +507,139 @@ kvd_status check_fused_args(const kvd_attn_shape* shape, const void* q, const vo
   return KVD_OK;
 }
 
+// The value-absorbed fused call (AbsorbArgs): its scratch, laid out after the
+// workspace's counters, fits the workspace of the tiled engines
+// (kvd_workspace_bytes), so no call needs a larger one.
+struct AbsorbPlan {
+  int32_t tile, Tp, S, n_tail;
+  size_t scores, rinv, u, uh, uml, tacc, tml, end;  // byte offsets from the workspace's start
+};
+
+// kvd_workspace_bytes of KVD_OP_FUSED: enough for any tiling, so that the size
+// grows with T_rec and T_tail whichever tile each call gets.
+size_t fused_ws_bytes(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_tail) {
+  size_t n = ws_plan_bytes(s, B, narrow_plan(s, T_rec, T_tail));
+  if (T_rec > 0 && wide_supported(s)) n = std::max(n, ws_plan_bytes(s, B, wide_plan(T_rec, T_tail)));
+  if (split_supported(s, T_rec, T_tail, kvd::kMtSplit))
+    n = std::max(n, ws_plan_bytes(s, B, split_plan(T_rec, kvd::kMtSplit)));
+  if (split_supported(s, T_rec, T_tail, 64)) n = std::max(n, ws_plan_bytes(s, B, split_plan(T_rec, 64)));
+  return n;
+}
+
+// Lays the plan out for S ranges.
+void absorb_layout(const kvd_attn_shape* s, int32_t B, int32_t S, AbsorbPlan* p) {
+  const size_t bq = (size_t)B * s->n_q_heads;
+  p->S = S;
+  p->scores = ws_done_bytes(s, B);
+  p->rinv = p->scores + kvd::align_up(4 * bq * p->Tp, 256);
+  p->u = p->rinv + kvd::align_up((size_t)4 * B * p->Tp, 256);
+  p->uh = p->u + (p->S > 1 ? kvd::align_up(4 * bq * p->S * ceil_div(s->d_model, kvd::kAbsorbCols) *
+                                               (kvd::kAbsorbCols + 2), 256) : 0);
+  p->uml = p->uh + kvd::align_up(4 * bq * s->d_model, 256);
+  p->tacc = p->uml + kvd::align_up(8 * bq, 256);
+  p->tml = p->tacc + kvd::align_up(4 * bq * p->n_tail * s->head_dim, 256);
+  p->end = p->tml + kvd::align_up(8 * bq * p->n_tail, 256);
+}
+
+// True and the plan when the call takes the value-absorbed path: automatic mode,
+// bf16 at head_dim 256, at most 16 query heads, d_model >= 1024 (the streamed read
+// costs as much as the value GEMM it replaces where d_model is short), and at
+// least kAbsorbMinTiles 64-token tiles of the call on the tiled engines.
+// Measured on both sides (Gemma-3-4B layer, whole step, packed weights): 128
+// tiles 44.7 us tiled against 47.7, 188 tiles 51.6 against 50.8, 256 tiles 59.8
+// against 54.4, 512 tiles 91 against 75.  At head_dim 128 (Qwen2.5-1.5B shape:
+// 2 KV heads, 12 query heads) the second read weighs as much as the saved GEMM:
+// 241.8 us tiled against 243.7 at B = 8 x 16384 tokens, 68.9 against 74.0 at
+// B = 8 x 4096.
+bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_tail, size_t ws_bytes, AbsorbPlan* p) {
+  if (g_fused_tokens.load(std::memory_order_relaxed) != 0 || s->dtype != KVD_BF16 || s->head_dim != 256) return false;
+  if (s->n_q_heads > 16 || s->d_model < kvd::kAbsorbMinD) return false;
+  if ((int64_t)s->n_kv_heads * B * ceil_div(T_rec, 64) < kvd::kAbsorbMinTiles) return false;
+  p->n_tail = kvd::absorb_tail_tiles(T_tail);
+  if (p->n_tail > kvd::kAbsorbMaxTail) return false;
+  // the score tile with the shortest whole rounds
+  const int64_t rows = (int64_t)s->n_kv_heads * s->head_dim;
+  p->tile = -1;
+  int64_t best_us = 0;
+  for (int32_t t = 0; t < kvd::kScoreTiles; ++t) {
+    if (rows % kvd::score_rows(t) != 0 ||
+        kvd::score_lds(s->head_dim, s->n_q_heads / s->n_kv_heads, kvd::score_rows(t), kvd::score_tokens(t),
+                       s->d_model).end > kvd::kLdsPerGroup)
+      continue;
+    const int64_t tiles = rows / kvd::score_rows(t) * B * ceil_div(T_rec, kvd::score_tokens(t));
+    if (tiles > INT32_MAX / 2) return false;
+    const int64_t us = (tiles + 255) / 256 * kvd::score_round_us(t, s->w_layout != KVD_W_ROWMAJOR);
+    if (p->tile < 0 || us < best_us) p->tile = t, best_us = us;
+  }
+  if (p->tile < 0) return false;
+  p->Tp = 128 * ceil_div(T_rec, 128);
+  const int64_t slices = ceil_div(s->d_model, kvd::kAbsorbCols);
+  if (slices * B * kvd::kAbsorbMaxRanges + (int64_t)p->n_tail * s->n_kv_heads * B > INT32_MAX) return false;
+  // ranges of a sequence: enough for about kAbsorbMinWgs workgroups, each at least
+  // 256 tokens, as far as the scratch and the arrival counters (two per
+  // completion word) allow
+  // (and the static scratch, so that the call without a workspace runs the same
+  // kernels)
+  const size_t limit = std::min({ws_bytes, fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes});
+  int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
+  if (slices > 2 * kvd::kSplitBitWords * s->n_kv_heads) want = 1;
+  for (int32_t S = want; S >= 1; --S) {
+    if (S > 1 && T_rec / S < 256) continue;
+    absorb_layout(s, B, S, p);
+    if (p->end <= limit) return true;
+  }
+  return false;
+}
+
 // The fused launch on validated arguments.  pos0 == nullptr: residual row 0 of
 // every sequence is at position 0.
 kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* h, int32_t h_ld, const void* gamma,
                         const void* w_k, const void* w_v, const int32_t* pos0, int32_t B, int32_t T_rec,
                         const kvd_kv_view* tail, int32_t T_tail, void* out, void* ws, size_t ws_bytes,
                         const kvd_kv_view* kv_debug, void* stream, const char* name) {
+  AbsorbPlan ap{};
+  if (out != nullptr && kv_debug == nullptr && ws != nullptr && (reinterpret_cast<uintptr_t>(ws) & 255u) == 0 &&
+      absorb_plan(shape, B, T_rec, T_tail, ws_bytes, &ap)) {
+    char* base = static_cast<char*>(ws);
+    kvd::AbsorbArgs a{};
+    a.q = q;
+    a.h = h;
+    a.h_ld = h_ld;
+    a.gamma = gamma;
+    a.w_k = w_k;
+    a.w_v = w_v;
+    a.pos0 = pos0;
+    if (T_tail > 0) {
+      a.tk = tail->k;
+      a.tv = tail->v;
+      a.tail_t_cap = tail->t_cap;
+      a.tail_t_off = tail->t_off;
+    }
+    a.T_tail = T_tail;
+    a.scores = reinterpret_cast<float*>(base + ap.scores);
+    a.rinv = reinterpret_cast<float*>(base + ap.rinv);
+    a.u = reinterpret_cast<float*>(base + ap.u);
+    a.uml = reinterpret_cast<float*>(base + ap.uml);
+    a.uh = reinterpret_cast<uint16_t*>(base + ap.uh);
+    // the arrival counters live in the completion words: two per 64-bit word
+    a.done = reinterpret_cast<unsigned*>(base + ws_ctr_bytes(shape, B));
+    a.done_ld = 2 * kvd::kSplitBitWords * shape->n_kv_heads;
+    a.fold = shape->w_layout == KVD_W_PACKED_GAMMA;
+    a.tacc = reinterpret_cast<float*>(base + ap.tacc);
+    a.tml = reinterpret_cast<float*>(base + ap.tml);
+    a.out = out;
+    a.d = shape->d_model;
+    a.n_q = shape->n_q_heads;
+    a.n_kv = shape->n_kv_heads;
+    a.B = B;
+    a.T = T_rec;
+    a.Tp = ap.Tp;
+    a.S = ap.S;
+    a.n_tail = ap.n_tail;
+    a.eps = shape->rms_eps;
+    fill_rev(shape, a.rev);
+    return device_status(kvd::launch_absorb(a, shape->w_layout, ap.tile, (hipStream_t)stream), name);
+  }
   const FusedPlan plan = fused_plan(shape, B, T_rec, T_tail);
   const int32_t S = plan.S;
   // one workgroup per (KV head, sequence, split), indexed in 32 bits
@@ -920,16 +1047,7 @@ int32_t kvd_set_fused_tokens(int32_t tokens) {
 size_t kvd_workspace_bytes(const kvd_attn_shape* shape, int32_t op, int32_t B, int32_t T_main, int32_t T_tail) {
   int32_t S = kvd_num_splits(shape, op, B, T_main, T_tail);
   if (S == 0) return 0;
-  // fused: enough for either tiling, so that the size grows with T_rec and
-  // T_tail whichever tile each call gets
-  if (op == KVD_OP_FUSED) {
-    size_t n = ws_plan_bytes(shape, B, narrow_plan(shape, T_main, T_tail));
-    if (T_main > 0 && wide_supported(shape)) n = std::max(n, ws_plan_bytes(shape, B, wide_plan(T_main, T_tail)));
-    if (split_supported(shape, T_main, T_tail, kvd::kMtSplit))
-      n = std::max(n, ws_plan_bytes(shape, B, split_plan(T_main, kvd::kMtSplit)));
-    if (split_supported(shape, T_main, T_tail, 64)) n = std::max(n, ws_plan_bytes(shape, B, split_plan(T_main, 64)));
-    return n;
-  }
+  if (op == KVD_OP_FUSED) return fused_ws_bytes(shape, B, T_main, T_tail);
   return ws_total(shape, B, S);
 }
 

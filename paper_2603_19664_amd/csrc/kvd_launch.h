@@ -61,6 +61,44 @@ struct FusedArgs {
   double rev[kMaxPairs];
 };
 
+// Fused recompute + attention with the value projection taken out of the token
+// loop (bf16, head_dim 256): V is linear in the residual, so
+//   sum_t p_t V_t = W_v sum_t p_t r_t (gamma * h_t),   r_t = 1 / rms(h_t),
+// and only the keys are recomputed per token.  Three launches:
+//   score_kernel   scores[b][h][t] = q_h . K_t (scaled into the log2 domain) and r_t;
+//   absorb_kernel  per (b, range s of the tokens, 128 columns of h): u[b][s][h] =
+//                  sum_t p_t r_t h_t and the range's (max, sum) in uml; the stored
+//                  tail's 64-row tiles attended into (tacc, tml) beside it;
+//   vproj_kernel   out = (W_v (gamma * sum_s w_s u_s) + sum_tail w acc) / sum w l.
+struct AbsorbArgs {
+  const void* q;
+  const void* h;
+  long long h_ld;
+  const void* gamma;
+  const void* w_k;
+  const void* w_v;
+  const int32_t* pos0;  // as FusedArgs::pos0
+  const void* tk;
+  const void* tv;
+  int tail_t_cap, tail_t_off, T_tail;
+  float* scores;  // [B][n_q][Tp]
+  float* rinv;    // [B][Tp]
+  float* u;       // S > 1: [B][slices][S] x (sums [n_q][128], (max, sum) [n_q][2])
+  uint16_t* uh;   // [B][n_q][2][d]: gamma * the merged sums as two bf16 parts
+  float* uml;     // [B][n_q][2]
+  unsigned* done; // S > 1: [B][done_ld] arrivals per slice (zero between calls)
+  int done_ld;
+  int fold;       // gamma is folded into the weights
+  float* tacc;    // [B][n_q][n_tail][hd]
+  float* tml;     // [B][n_q][n_tail][2]
+  void* out;
+  int d, n_q, n_kv, B, T, Tp, S, n_tail;
+  float eps;
+  double rev[kMaxPairs];
+};
+// tile: a ScoreTile (kvd_layout.h).
+hipError_t launch_absorb(const AbsorbArgs& a, int layout, int tile, hipStream_t st);
+
 // Split-K attention over stored K/V.  fp32: S = decode_splits(T) chunks of
 // kTile keys (decode_kernel).  bf16: S splits of the nblk 16-key blocks
 // (sa_first_block), one streaming workgroup each (stream_attn_kernel).  out == nullptr:

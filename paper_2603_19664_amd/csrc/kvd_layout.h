@@ -239,6 +239,28 @@ constexpr size_t fused_pair_lds_bytes(int g) {
       .end;
 }
 
+constexpr int kScoreHeads = 8;     // query heads of a KV head per pass of the score epilogue
+// LDS of the score kernel: RoPE table, 1/rms and positions, the staging ring
+// (reused for the epilogue's partial dot products), the heads' query rows
+// (fp32, scaled), gamma.
+struct ScoreLds {
+  size_t rev, rinv, pos, hst, q, gam, end;
+};
+constexpr ScoreLds score_lds(int hd, int g, int rows, int mt, int d) {
+  ScoreLds L{};
+  L.rev = 0;
+  L.rinv = align_up(L.rev + sizeof(double) * kMaxPairs, 16);
+  L.pos = align_up(L.rinv + sizeof(float) * mt, 16);
+  L.hst = align_up(L.pos + sizeof(int) * mt, 16);
+  const size_t ring = sizeof(uint16_t) * kDepth * mt * kKT;
+  const size_t red = sizeof(float) * (rows / 32) * kScoreHeads * mt;
+  L.q = align_up(L.hst + (ring > red ? ring : red), 16);
+  const int nh = rows > hd ? rows / hd : 1;
+  L.gam = align_up(L.q + sizeof(float) * nh * g * hd, 16);
+  L.end = L.gam + gamma_lds_bytes(d);
+  return L;
+}
+
 // Streaming projection (current-token q/K/V): one workgroup of kStreamWaves
 // waves per 32 weight rows.  Waves 1.. keep kStreamDepth chunks of the rows'
 // MFMA A fragments in flight in registers and write each chunk (kStreamChunk
@@ -357,6 +379,33 @@ constexpr SaLds sa_lds(int hd, int G) {
   L.end = align_up(L.ctr + sizeof(unsigned long long), 16);
   return L;
 }
+
+// Value-absorbed fused attention (AbsorbArgs; head_dim 256).  Score tiles: K rows
+// x tokens per workgroup.
+enum ScoreTile { kScore512x64 = 0, kScore256x128 = 1, kScore256x64 = 2, kScoreTiles = 3 };
+constexpr int score_rows(int tile) { return tile == kScore512x64 ? 512 : 256; }
+constexpr int score_tokens(int tile) { return tile == kScore256x128 ? 128 : 64; }
+// Time of one round of 256 score tiles (us at d 2560: 217, 222 and 265 us for the
+// 5, 5 and 10 rounds of B = 16 x 2560 tokens with packed weights, 507, 316 and 557
+// row-major).
+constexpr int score_round_us(int tile, bool packed) {
+  return tile == kScore512x64 ? (packed ? 43 : 101) : tile == kScore256x128 ? (packed ? 45 : 63) : (packed ? 27 : 56);
+}
+constexpr int kAbsorbCols = 128;   // residual columns per absorb workgroup
+constexpr int kAbsorbWaves = 4;
+constexpr int kAbsorbBlock = 32;   // tokens per wave step
+constexpr int kAbsorbMaxTail = 128;  // stored-tail tiles (their partials sit in the scratch)
+constexpr int kAbsorbDepth = 3;      // wave steps in flight, the one being added included (4 spilled)
+constexpr int kAbsorbMaxRanges = 8;
+// Workgroups that the number of ranges aims for (Gemma-3-4B layer): B = 1 x 4096
+// tokens take 25, 18, 15, 13.8, 13.4 us with 1..5 ranges of 20 workgroups; B = 8
+// x 3072 (160 workgroups with one range) 32 us with 1 range, 38 with 2.
+constexpr int kAbsorbMinWgs = 160;
+constexpr int kAbsorbMinTiles = 192;
+constexpr int kAbsorbMinD = 1024;
+constexpr int kVprojWaves = 16;
+// 64-row tiles of a stored tail (a remainder of at most 4 rows joins the tile before it).
+constexpr int absorb_tail_tiles(int T_tail) { return T_tail > 0 ? decode_splits<uint16_t>(T_tail) : 0; }
 
 // Bytes of the static per-device scratch of kvd_fused_recompute_attn_noalloc:
 // enough for the split-K workspace of every measured workload (the largest,

@@ -1,0 +1,182 @@
+"""The value-absorbed fused path (kvd_fused_recompute_attn in automatic mode, bf16,
+head_dim 256, d_model >= 1024, at least 192 64-token tiles, a scratch that fits
+the tiled engines' workspace) against the fp64
+oracle and the tiled engines, at the edges of its tiles: ragged token tiles and
+32-token steps, a last half column slice, one and several ranges per sequence,
+packed and split query-head rows, every kind of stored tail, each score tile.
+
+Tolerance: as the tiled engines', 2e-2 of the largest value; the 2-norm error
+against the oracle is besides no larger than the tiled engine's (keys and values
+are rounded there and not here) plus a tenth."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2603_19664_amd import configs as C
+from paper_2603_19664_amd import kvd
+
+from gpu_cases import empty_kv, err, f64, gpu_fused, gpu_project, gpu_recompute, make_layer, note, oracle_decode
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    note(f"[gpu] {request.node.nodeid}")
+    yield
+    torch.cuda.synchronize()
+    kvd.kvd_set_fused_tokens(0)
+
+
+def _bits(t):
+    return t.view(torch.int16)
+
+
+def _layer(B, T, d=1024, n_q=8, n_kv=4, **kw):
+    return make_layer(C.GEMMA3_4B, B=B, T=T, seed=B + T + d, d_model=d, n_q=n_q, n_kv=n_kv,
+                      pos0=[(37 * b) % 1000 for b in range(B)], **kw)
+
+
+def _rel(x, ref):
+    x = f64(x) if isinstance(x, torch.Tensor) else x
+    return float(np.linalg.norm(x - ref) / np.linalg.norm(ref))
+
+
+def _counters(ws, L):
+    s = L.shape
+    n = -(-L.B * s.n_kv_heads * 8 // 256) * 256 + -(-L.B * s.n_kv_heads * 4 * 8 // 256) * 256
+    return int(torch.count_nonzero(ws[:n]))
+
+
+@pytest.mark.parametrize("packed", [False, True, "gamma"])
+@pytest.mark.parametrize("B,T,d,n_q,n_kv", [
+    (7, 450, 1024, 8, 4),     # ragged tiles, one range, 2 query heads per KV head
+    (7, 449, 1088, 8, 4),     # a last half column slice, one token past a tile
+    (4, 449, 1024, 16, 8),    # 16 query heads: two-part rows
+    (8, 512, 1024, 9, 3),     # 768 K rows: 256-row tiles only
+    (24, 500, 1024, 5, 1),    # one KV head
+    (1, 3101, 1024, 8, 4),    # several ranges, a ragged last step
+    (3, 1025, 1216, 16, 4)])  # several ranges, 16 query heads, half slice
+def test_absorbed_vs_oracle(B, T, d, n_q, n_kv, packed):
+    L = _layer(B, T, d, n_q, n_kv, packed=packed)
+    q, _, out, _ = gpu_fused(L)
+    sel = sorted({0, B // 2, B - 1})
+    ref = oracle_decode(L, b_sel=sel)
+    e = err(f64(out[sel]), ref)
+    kvd.kvd_set_fused_tokens(64)
+    _, _, tiled, _ = gpu_fused(L, q=q)
+    r, rt = _rel(out[sel], ref), _rel(tiled[sel], ref)
+    note(f"    err {e:.3e}, 2-norm {r:.3e} (tiled {rt:.3e})")
+    assert e < TOL and r <= 1.1 * rt
+    assert not torch.equal(_bits(out), _bits(tiled))  # the absorbed path ran
+    assert err(f64(out), f64(tiled)) < TOL
+
+
+@pytest.mark.parametrize("T_tail,t_cap,t_off", [(0, 1, 0), (1, 1, 0), (4, 7, 5), (5, 9, 2), (64, 64, 63), (68, 100, 60),
+                                                (70, 80, 33), (200, 211, 150)])
+def test_absorbed_stored_tail(T_tail, t_cap, t_off):
+    # a ring of t_cap slots read from slot t_off, wrapping: rows T .. T + T_tail - 1
+    B, T, d = 7, 450, 1024
+    L = _layer(B, T + T_tail, d)
+    s = L.shape
+    K, V = gpu_recompute(L)
+    rk, rv = empty_kv(L, t_cap)
+    for i in range(T_tail):
+        rk[:, :, (t_off + i) % t_cap] = K[:, :, T + i]
+        rv[:, :, (t_off + i) % t_cap] = V[:, :, T + i]
+    q = gpu_project(L)
+
+    def run(mode):
+        kvd.kvd_set_fused_tokens(mode)
+        ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, T_tail)
+        outs = []
+        for _ in range(2):
+            o = torch.empty_like(q)
+            kvd.kvd_fused_recompute_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, o, ws,
+                                         rk if T_tail else None, rv if T_tail else None, T_tail, t_off)
+            outs.append(o)
+        assert torch.equal(_bits(outs[0]), _bits(outs[1])) and _counters(ws, L) == 0
+        return outs[0]
+
+    out, tiled = run(0), run(64)
+    sel = [0, 6]
+    pos = f64(L.pos0)[sel][:, None] + np.arange(T)[None, :]
+    ref = O.kv_direct_decode(f64(q)[sel], f64(L.h[sel, :T]), f64(L.gamma), f64(L.w_k), f64(L.w_v), pos,
+                             f64(K[sel, :, T:]) if T_tail else None, f64(V[sel, :, T:]) if T_tail else None,
+                             s.n_kv_heads, s.head_dim, s.rms_eps, s.rope_theta)
+    e, r, rt = err(f64(out[sel]), ref), _rel(out[sel], ref), _rel(tiled[sel], ref)
+    note(f"    err {e:.3e}, 2-norm {r:.3e} (tiled {rt:.3e})")
+    assert e < TOL and r <= 1.1 * rt and not torch.equal(_bits(out), _bits(tiled))
+
+
+@pytest.mark.parametrize("B,T,n_q,n_kv,packed", [(16, 1000, 8, 4, True), (16, 1000, 8, 4, False),
+                                                 (9, 2048, 8, 8, True), (5, 1500, 6, 3, True), (2, 3000, 8, 4, "gamma")])
+def test_absorbed_score_tiles(B, T, n_q, n_kv, packed):
+    # grids on both sides of the score tiles' rule (512 x 64, 256 x 128, 256 x 64), and
+    # the call without a workspace argument
+    L = _layer(B, T, 1024, n_q, n_kv, packed=packed)
+    s = L.shape
+    q, (tk, tv), out, _ = gpu_fused(L)
+    na = torch.empty_like(out)
+    kvd.kvd_fused_recompute_attn_noalloc(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, na, tk, tv, 1)
+    assert torch.equal(_bits(out), _bits(na))
+    kvd.kvd_set_fused_tokens(64)
+    _, _, tiled, _ = gpu_fused(L, q=q)
+    ref = oracle_decode(L, b_sel=[B - 1])
+    e, r, rt = err(f64(out), f64(tiled)), _rel(out[B - 1:], ref), _rel(tiled[B - 1:], ref)
+    note(f"    vs tiled {e:.3e}, 2-norm vs oracle {r:.3e} (tiled {rt:.3e})")
+    assert e < TOL and r <= 1.1 * rt and not torch.equal(_bits(out), _bits(tiled))
+
+
+def test_absorbed_window_and_longer_store():
+    # a window over a longer checkpoint store (row stride h_ld > T), positions from 0
+    B, T, W = 7, 900, 451
+    L = _layer(B, T, 1024)
+    s = L.shape
+    q = torch.empty((B, s.n_q_heads, s.head_dim), dtype=s.torch_dtype, device="cuda")
+    tk, tv = empty_kv(L, 1)
+    pos = torch.full((B,), W - 1, dtype=torch.int32, device="cuda")
+    kvd.kvd_project_qkv(s, L.h_new, L.gamma, L.lw_q, L.lw_k, L.lw_v, pos, q, tk, tv, 0)
+    out = torch.empty_like(q)
+    ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, W - 1, 1)
+    kvd.kvd_fused_window_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, W, out, ws, tk, tv, 1)
+    sel = [0, B - 1]
+    ref = O.sliding_window_decode(f64(L.h_new[sel]), f64(L.h[sel, :T]), f64(L.gamma), f64(L.w_q), f64(L.w_k),
+                                  f64(L.w_v), W, s.n_q_heads, s.n_kv_heads, s.head_dim, s.rms_eps, s.rope_theta)
+    assert err(f64(out[sel]), ref) < TOL
+
+
+def test_workspace_too_small_for_the_absorbed_scratch():
+    # a workspace that holds only the tiled engine's splits was accepted before and
+    # still is: the call runs on the tiled engine
+    L = _layer(7, 450)
+    s = L.shape
+    q, (tk, tv), _, _ = gpu_fused(L)
+    S = kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, L.B, L.T, 1)
+    up = lambda x: -(-x // 256) * 256  # noqa: E731
+    n = (up(L.B * s.n_kv_heads * 8) + up(L.B * s.n_kv_heads * 32) + up(L.B * s.n_q_heads * S * s.head_dim * 4)
+         + up(L.B * s.n_q_heads * S * 8))
+    out, tiled = torch.empty_like(q), torch.empty_like(q)
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    kvd.kvd_fused_recompute_attn(s, q, L.h, L.T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, tk, tv, 1)
+    kvd.kvd_set_fused_tokens(64)
+    kvd.kvd_fused_recompute_attn(s, q, L.h, L.T, L.gamma, L.lw_k, L.lw_v, L.pos0, tiled, ws, tk, tv, 1)
+    assert err(f64(out), f64(tiled)) < TOL and _counters(ws, L) == 0
+
+
+def test_absorbed_under_capture():
+    L = _layer(1, 3101)
+    s = L.shape
+    q, (tk, tv), ref, _ = gpu_fused(L)
+    ws = kvd.workspace(s, kvd.KVD_OP_FUSED, 1, L.T, 1)
+    out = torch.empty_like(q)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        kvd.kvd_fused_recompute_attn(s, q, L.h, L.T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, tk, tv, 1)
+    for _ in range(4):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(_bits(out), _bits(ref))
