@@ -8,7 +8,7 @@
 //                  (features = MFMA rows), the normalised residuals the B operand
 //                  (tokens = MFMA columns), so each lane ends up holding whole RoPE
 //                  pairs (2i, 2i+1) of one token.
-//  * F32Tile:      the same contraction in fp32 on the vector ALUs.
+//  * F32Tile:      the same contraction in fp32 on v_mfma_f32_16x16x4_f32.
 //  * epilogues:    1/rms row scale, RoPE on key rows (Sec. 3.2, Eqs. rope_cos /
 //                  rope_sin), one rounding to the storage type, into an LDS tile
 //                  [tokens][K | V].
@@ -826,90 +826,130 @@ struct WideTile {
   }
 };
 
-// ------------------------------------------------------------------ fp32 VALU tile
+// ------------------------------------------------------------------ fp32 tile
 
-// The same contraction in fp32 on the vector ALUs: thread (pair p, token group)
-// accumulates rows 2p, 2p+1 of the 2*HD rows for TPT tokens, in d order.
+// The contraction in fp32 on v_mfma_f32_16x16x4_f32 (full fp32 products and
+// sums): a wave owns NBF blocks of 16 weight rows (A) and NBT blocks of 16 tokens
+// (B).  Both operands come straight from global memory, 16 bytes per lane: lane
+// group lg = lane / 16 holds k = 16 c + 4 lg .. + 3 of its row, and MFMA e of
+// chunk c takes element e of every lane, so an element's chain runs over d in
+// the order k = 16 c + 4 (0..3) + e.  Every fp32 producer of q, K and V (any
+// NBF, NBT) has this one chain, hence bit-identical values.  The sum of squares
+// of a token is four chains (one per lane group, in k order) added by a fixed
+// xor tree; each wave keeps its own, so nothing passes through LDS.
+// R chunks are in flight.
+template <int NBF, int NBT, int R>
+__device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const float* const (&hrow)[NBT],
+                                         const float* gam, int d, float eps, f32x4_t (&acc)[NBF][NBT],
+                                         float (&rinv)[NBT]) {
+  const int nc = d / 16;
+  float ss[NBT];
+#pragma unroll
+  for (int t = 0; t < NBT; ++t) {
+    ss[t] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) acc[i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  f32x4_t A[R][NBF], B[R][NBT], G[R];
+  auto load = [&](int slot, int c) {
+    const int o = 16 * min(c, nc - 1);
+    G[slot] = *reinterpret_cast<const f32x4_t*>(gam + o);
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) A[slot][i] = *reinterpret_cast<const f32x4_t*>(wrow[i] + o);
+#pragma unroll
+    for (int t = 0; t < NBT; ++t) B[slot][t] = *reinterpret_cast<const f32x4_t*>(hrow[t] + o);
+  };
+#pragma unroll
+  for (int r = 0; r < R - 1; ++r) load(r, r);
+  for (int c0 = 0; c0 < nc; c0 += R) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      load((r + R - 1) % R, c0 + r + R - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (c0 + r < nc) {
+        f32x4_t x[NBT];
+#pragma unroll
+        for (int t = 0; t < NBT; ++t) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ss[t] = fmaf(B[r][t][e], B[r][t][e], ss[t]);
+          x[t] = B[r][t] * G[r];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < NBF; ++i)
+#pragma unroll
+            for (int t = 0; t < NBT; ++t)
+              acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][i][e], x[t][e], acc[i][t], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NBT; ++t) {
+    float v = ss[t];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    rinv[t] = 1.0f / sqrtf(v / (float)d + eps);
+  }
+}
+
+// One lane's 4 features f0 .. f0 + 3 of a token: 1/rms, then RoPE on rotated rows.
+__device__ __forceinline__ float4 f32_finish(const f32x4_t& a, float ri, int rope, int p, const double* rev, int f0) {
+  float v[4] = {a[0] * ri, a[1] * ri, a[2] * ri, a[3] * ri};
+  if (rope) {
+    rope_rotate(v[0], v[1], p, rev[f0 >> 1]);
+    rope_rotate(v[2], v[3], p, rev[(f0 >> 1) + 1]);
+  }
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// The fused kernel's fp32 tile: 8 waves, wave w owns the 16-row blocks w, w + 8,
+// .. of the 2 * HD rows (K rows, then V rows) for all MT tokens of the tile,
+// which go to the LDS tile [MT][K | V].  MFMA-bound on its CU (64 tokens of
+// head_dim 64 at d 576: 37k cycles).
 template <int HD, int MT>
 struct F32Tile {
   static constexpr int NT = kNtTile;
-  static constexpr int TG = NT / HD;         // token groups
-  static constexpr int TPT = MT / TG;        // tokens per thread
-  static constexpr int CPT = MT * 8 / NT;
-  static constexpr int HLD = h_ld<float>();
+  static constexpr int NBF = 2 * HD / 16 / (NT / 64);
+  static constexpr int NBT = MT / 16;
   static constexpr int KLD = kv_ld<float>(HD);
 
-  // setup(): the caller's LDS writes of pos and rev (read after the K-loop's
-  // barriers), run first.
+  // h_tile: the tile's n <= MT rows (tokens past n read row 0 and get K = V = 0).
+  // setup(): the caller's LDS writes of pos and rev.
   template <class Setup>
-  static __device__ __forceinline__ void run(const float* const (&hrow)[CPT], const bool (&valid)[CPT], const float* gamma, int d,
-                             float eps, const Half (&halves)[2], float* hst, float* rinv, const int* pos,
-                             const double* rev, float* kv, const Setup& setup) {
-    setup();
-    const int tid = threadIdx.x, sub = tid & 7;
-    const int p = tid % HD;
-    const int tg = tid / HD;
-    const int half = (2 * p) / HD;
-    const int r0 = (2 * p) % HD;
-    const float* w = static_cast<const float*>(half ? halves[1].w : halves[0].w);
-    const float* w0 = w ? w + (size_t)r0 * d : nullptr;
-    const int nsteps = d / kKT;
-
-    float ss[CPT];
+  static __device__ __forceinline__ void run(const float* h_tile, int n, const float* gamma, int d, float eps,
+                                             const Half (&halves)[2], const int* pos, const double* rev, float* kv,
+                                             const Setup& setup) {
+    const int lane = threadIdx.x & 63, w = wave_id();
+    const int lq = lane & 15, lg = lane >> 4;
+    const float* const w0 = static_cast<const float*>(halves[0].w);
+    const float* const w1 = static_cast<const float*>(halves[1].w);
+    const float* wrow[NBF];
+    const float* hrow[NBT];
 #pragma unroll
-    for (int r = 0; r < CPT; ++r) ss[r] = 0.0f;
-    float acc0[TPT], acc1[TPT];
-#pragma unroll
-    for (int t = 0; t < TPT; ++t) acc0[t] = acc1[t] = 0.0f;
-
-    for (int s = 0; s < nsteps; ++s) {
-      float g[8];
-      load8(gamma + (size_t)s * kKT + 8 * sub, g);
-#pragma unroll
-      for (int r = 0; r < CPT; ++r) {
-        float x[8];
-        load8(hrow[r] + (size_t)s * kKT, x);
-        float* dst = hst + (size_t)((tid >> 3) + (NT / 8) * r) * HLD + 8 * sub;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float xe = valid[r] ? x[e] : 0.0f;
-          ss[r] = fmaf(xe, xe, ss[r]);
-          dst[e] = xe * g[e];
-        }
-      }
-      __syncthreads();
-      if (w0) {
-#pragma unroll 4
-        for (int k4 = 0; k4 < kKT / 4; ++k4) {
-          const float4 wa = *reinterpret_cast<const float4*>(w0 + (size_t)s * kKT + 4 * k4);
-          const float4 wb = *reinterpret_cast<const float4*>(w0 + d + (size_t)s * kKT + 4 * k4);
-#pragma unroll
-          for (int t = 0; t < TPT; ++t) {
-            const float4 hv = *reinterpret_cast<const float4*>(hst + (size_t)(tg * TPT + t) * HLD + 4 * k4);
-            acc0[t] = fmaf(wa.x, hv.x, acc0[t]);
-            acc0[t] = fmaf(wa.y, hv.y, acc0[t]);
-            acc0[t] = fmaf(wa.z, hv.z, acc0[t]);
-            acc0[t] = fmaf(wa.w, hv.w, acc0[t]);
-            acc1[t] = fmaf(wb.x, hv.x, acc1[t]);
-            acc1[t] = fmaf(wb.y, hv.y, acc1[t]);
-            acc1[t] = fmaf(wb.z, hv.z, acc1[t]);
-            acc1[t] = fmaf(wb.w, hv.w, acc1[t]);
-          }
-        }
-      }
-      __syncthreads();
+    for (int i = 0; i < NBF; ++i) {
+      const int r = 16 * (w + 8 * i) + lq;
+      wrow[i] = (r < HD ? w0 + (size_t)r * d : w1 + (size_t)(r - HD) * d) + 4 * lg;
     }
-
-    finish_rms<NT, CPT>(ss, valid, d, eps, rinv);
-    __syncthreads();
-
 #pragma unroll
-    for (int t = 0; t < TPT; ++t) {
-      const int tok = tg * TPT + t;
-      const float ri = rinv[tok];
-      float v0 = acc0[t] * ri, v1 = acc1[t] * ri;
-      if (half ? halves[1].rope : halves[0].rope) rope_rotate(v0, v1, pos[tok], rev[r0 >> 1]);
-      *reinterpret_cast<float2*>(kv + (size_t)tok * KLD + half * HD + r0) = make_float2(v0, v1);
+    for (int t = 0; t < NBT; ++t) hrow[t] = h_tile + (size_t)(16 * t + lq < n ? 16 * t + lq : 0) * d + 4 * lg;
+    setup();
+    f32x4_t acc[NBF][NBT];
+    float rinv[NBT];
+    f32_rows<NBF, NBT, NBF == 1 ? 4 : 3>(wrow, hrow, gamma + 4 * lg, d, eps, acc, rinv);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NBT; ++t) {
+      const int tok = 16 * t + lq;
+      const int p = pos[tok];
+      const float ri = tok < n ? rinv[t] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < NBF; ++i) {
+        const int r = 16 * (w + 8 * i), half = r >= HD, f0 = r - half * HD + 4 * lg;
+        *reinterpret_cast<float4*>(kv + (size_t)tok * KLD + half * HD + f0) =
+            f32_finish(acc[i][t], ri, half ? halves[1].rope : halves[0].rope, p, rev, f0);
+      }
     }
   }
 };

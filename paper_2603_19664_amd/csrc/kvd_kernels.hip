@@ -34,9 +34,10 @@ namespace kvd {
 
 // grid: xcd_map(n_units * n_tiles) workgroups; item = unit * n_tiles + tile, so
 // the token tiles of one KV head (which share W_k / W_v) run on one XCD.
-template <typename T, int HD, int MT, bool PACKED, bool FOLD>
+template <int HD, int MT, bool PACKED, bool FOLD>
 __global__ __launch_bounds__(kNtTile, 1) void proj_kernel(ProjArgs a, int per_xcd, int n_tiles, int n_units) {
   extern __shared__ __align__(16) char lds[];
+  using T = uint16_t;
   constexpr int NT = kNtTile;
   constexpr ProjLds PL = proj_lds<T>(HD, MT);
   constexpr int CPT = MT * 8 / NT;
@@ -98,13 +99,8 @@ __global__ __launch_bounds__(kNtTile, 1) void proj_kernel(ProjArgs a, int per_xc
     hrow[r] = static_cast<const T*>(a.h) + ((size_t)b * a.h_ld + t) * a.d + 8 * (tid & 7);
   }
 
-  if constexpr (sizeof(T) == 2) {
-    MfmaTile<HD, MT, PACKED, FOLD>::run(hrow, valid, gam, static_cast<const uint16_t*>(a.gamma), a.d, a.eps, halves,
-                                        hst, rinv, pos, rev, kv, setup);
-  } else {
-    F32Tile<HD, MT>::run(hrow, valid, static_cast<const float*>(a.gamma), a.d, a.eps, halves, hst, rinv, pos, rev,
-                         kv, setup);
-  }
+  MfmaTile<HD, MT, PACKED, FOLD>::run(hrow, valid, gam, static_cast<const uint16_t*>(a.gamma), a.d, a.eps, halves,
+                                      hst, rinv, pos, rev, kv, setup);
   __syncthreads();
 
   // store: 16-byte chunks of each valid token row of each present half.
@@ -128,6 +124,58 @@ __global__ __launch_bounds__(kNtTile, 1) void proj_kernel(ProjArgs a, int per_xc
     }
     *reinterpret_cast<uint4*>(dst + ch * CH) =
         *reinterpret_cast<const uint4*>(kv + (size_t)row * KLD + half * HD + ch * CH);
+  }
+}
+
+// ------------------------------------------------------------------ fp32 projections
+
+// fp32 q / K / V of B * T token rows: one wave per 16 weight rows x 16 NBT
+// tokens (f32_rows), its results stored straight to global memory.  Row blocks
+// in order: the K rows of n_kv_units heads, their V rows, then the n_q query
+// heads' rows (q != 0).  grid: (row blocks / NW) * token blocks; a workgroup's
+// NW waves share its tokens.  At one token the launch is a chain of d / 4
+// dependent MFMAs (about 3 us at d 576).
+template <int HD, int NBT, int NW, int R>
+__global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb) {
+  __shared__ double rev[HD / 2];
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int lq = lane & 15, lg = lane >> 4;
+  for (int i = threadIdx.x; i < HD / 2; i += 64 * NW) rev[i] = a.rev[i];
+  __syncthreads();
+  const int rg = blockIdx.x / n_tb, tb = blockIdx.x - rg * n_tb;
+  const int row = 16 * (rg * NW + w), kv_rows = a.n_kv_units * HD;
+  const int mat = row < kv_rows ? 1 : row < 2 * kv_rows ? 2 : 0;
+  const int r0 = row - (mat == 1 ? 0 : mat == 2 ? kv_rows : 2 * kv_rows);  // first row in its matrix
+  const float* wm = static_cast<const float*>(mat == 1 ? a.w_k : mat == 2 ? a.w_v : a.w_q);
+  const float* const wrow[1] = {wm + (size_t)(r0 + lq) * a.d + 4 * lg};
+  const long long ntok = (long long)a.B * a.T, n0 = (long long)tb * 16 * NBT;
+  const float* hrow[NBT];
+  int b[NBT], t[NBT];
+  bool ok[NBT];
+#pragma unroll
+  for (int k = 0; k < NBT; ++k) {
+    const long long n = n0 + 16 * k + lq;
+    ok[k] = n < ntok;
+    const long long nn = ok[k] ? n : n0;  // tokens past the end repeat a row and are not stored
+    b[k] = (int)(nn / a.T);
+    t[k] = (int)(nn - (long long)b[k] * a.T);
+    hrow[k] = static_cast<const float*>(a.h) + ((size_t)b[k] * a.h_ld + t[k]) * a.d + 4 * lg;
+  }
+  f32x4_t acc[1][NBT];
+  float rinv[NBT];
+  f32_rows<1, NBT, R>(wrow, hrow, static_cast<const float*>(a.gamma) + 4 * lg, a.d, a.eps, acc, rinv);
+  const int head = r0 / HD, f0 = r0 % HD + 4 * lg;
+#pragma unroll
+  for (int k = 0; k < NBT; ++k) {
+    if (!ok[k]) continue;
+    const float4 v = f32_finish(acc[0][k], rinv[k], mat != 2, a.pos0[b[k]] + t[k], rev, f0);
+    float* dst;
+    if (mat == 0)
+      dst = static_cast<float*>(a.q_out) + (((size_t)b[k] * a.T + t[k]) * a.n_q + head) * HD;  // [B][T][n_q][hd]
+    else
+      dst = static_cast<float*>(mat == 1 ? a.k_out : a.v_out) +
+            (((size_t)b[k] * a.n_kv + head) * a.kv_t_cap + a.kv_t_off + t[k]) * HD;
+    *reinterpret_cast<float4*>(dst + f0) = v;
   }
 }
 
@@ -645,8 +693,8 @@ __device__ __forceinline__ void fused_body(const FusedArgs& a, int per_xcd, int 
       MfmaTile<HD, MT, PACKED, FOLD>::run(hrow, valid, gam, static_cast<const uint16_t*>(a.gamma), a.d, a.eps, halves,
                                           hst, rinv, pos, rev, kv, setup);
     } else {
-      F32Tile<HD, MT>::run(hrow, valid, static_cast<const float*>(a.gamma), a.d, a.eps, halves, hst, rinv, pos, rev,
-                           kv, setup);
+      F32Tile<HD, MT>::run(static_cast<const float*>(a.h) + ((size_t)b * a.h_ld + t0) * a.d, n,
+                           static_cast<const float*>(a.gamma), a.d, a.eps, halves, pos, rev, kv, setup);
     }
     __syncthreads();
     if (a.dbg_k != nullptr) {
@@ -1374,12 +1422,12 @@ static hipError_t ensure_lds(K kernel, size_t bytes, std::atomic<size_t>& done) 
 
 // Launcher templates take the weight layout L: 0 row-major, 1 packed, 2 packed
 // with gamma folded in (kvd_weight_layout).
-template <typename T, int HD, int L>
+template <int HD, int L>
 static hipError_t proj_t(const ProjArgs& a, int n_units, hipStream_t st) {
-  constexpr int MT = sizeof(T) == 2 ? kMtBf16 : kMtF32;
-  const size_t bytes = proj_lds<T>(HD, MT).end + gamma_lds_bytes(a.d);
+  constexpr int MT = kMtBf16;
+  const size_t bytes = proj_lds<uint16_t>(HD, MT).end + gamma_lds_bytes(a.d);
   static std::atomic<size_t> done{0};
-  auto k = proj_kernel<T, HD, MT, L != 0, L == 2>;
+  auto k = proj_kernel<HD, MT, L != 0, L == 2>;
   hipError_t e = ensure_lds(k, bytes, done);
   if (e != hipSuccess) return e;
   const long long ntok = (long long)a.B * a.T;
@@ -1387,6 +1435,25 @@ static hipError_t proj_t(const ProjArgs& a, int n_units, hipStream_t st) {
   const XcdMap m = xcd_map((long long)n_units * n_tiles);
   hipLaunchKernelGGL(k, dim3(m.grid), dim3(kNtTile), bytes, st, a, m.per, n_tiles, n_units);
   return hipGetLastError();
+}
+
+template <int HD, int NBT, int NW, int R>
+static hipError_t f32_proj_nt(const ProjArgs& a, int rows, hipStream_t st) {
+  const long long n_tb = ((long long)a.B * a.T + 16 * NBT - 1) / (16 * NBT);
+  const long long grid = n_tb * (rows / (16 * NW));
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((f32_proj_kernel<HD, NBT, NW, R>), dim3((unsigned)grid), dim3(64 * NW), 0, st, a, (int)n_tb);
+  return hipGetLastError();
+}
+
+// One wave per workgroup and 16 tokens while that is at most about one wave per
+// SIMD (the current token); else 64 rows x 32 tokens per workgroup.
+template <int HD>
+static hipError_t f32_proj_t(const ProjArgs& a, int n_units, hipStream_t st) {
+  const int rows = 2 * a.n_kv_units * HD + (n_units > a.n_kv_units ? a.n_q * HD : 0);
+  const long long waves = (long long)(rows / 16) * (((long long)a.B * a.T + 15) / 16);
+  if (waves <= 1024) return f32_proj_nt<HD, 1, 1, 12>(a, rows, st);
+  return f32_proj_nt<HD, 2, 4, 6>(a, rows, st);
 }
 
 template <int HD, int L>
@@ -1589,8 +1656,8 @@ hipError_t launch_proj(const ProjArgs& a, int dtype_bf16, int hd, int layout, in
                        : proj_split_t<128, kMtSplit, split_nt(128), 128, L>(a, n_units, st);
     });
   }
-#define PB(H) with_layout(layout, [&](auto lc) { return proj_t<uint16_t, H, decltype(lc)::value>(a, n_units, st); })
-#define PF(H) proj_t<float, H, 0>(a, n_units, st)
+#define PB(H) with_layout(layout, [&](auto lc) { return proj_t<H, decltype(lc)::value>(a, n_units, st); })
+#define PF(H) f32_proj_t<H>(a, n_units, st)
   KVD_DISPATCH(dtype_bf16, hd, PB, PF)
 #undef PB
 #undef PF
