@@ -859,32 +859,148 @@ __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const 
 #pragma unroll
     for (int t = 0; t < NBT; ++t) B[slot][t] = *reinterpret_cast<const f32x4_t*>(hrow[t] + o);
   };
+  auto step = [&](int r) {
+    f32x4_t x[NBT];
+#pragma unroll
+    for (int t = 0; t < NBT; ++t) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss[t] = fmaf(B[r][t][e], B[r][t][e], ss[t]);
+      x[t] = B[r][t] * G[r];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < NBF; ++i)
+#pragma unroll
+        for (int t = 0; t < NBT; ++t)
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][i][e], x[t][e], acc[i][t], 0, 0, 0);
+  };
 #pragma unroll
   for (int r = 0; r < R - 1; ++r) load(r, r);
-  for (int c0 = 0; c0 < nc; c0 += R) {
+  // whole groups of R chunks without a branch inside, so that the waits count
+  // the loads in flight (with a bound check per chunk the compiler drained them
+  // all once per group: 19 us instead of 12 for the 1000-token prefill)
+  int c0 = 0;
+  for (; c0 + R <= nc; c0 += R) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       load((r + R - 1) % R, c0 + r + R - 1);
       __builtin_amdgcn_sched_barrier(0);
-      if (c0 + r < nc) {
-        f32x4_t x[NBT];
-#pragma unroll
-        for (int t = 0; t < NBT; ++t) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ss[t] = fmaf(B[r][t][e], B[r][t][e], ss[t]);
-          x[t] = B[r][t] * G[r];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < NBF; ++i)
-#pragma unroll
-            for (int t = 0; t < NBT; ++t)
-              acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][i][e], x[t][e], acc[i][t], 0, 0, 0);
-      }
+      step(r);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+#pragma unroll
+  for (int r = 0; r < R - 1; ++r)
+    if (c0 + r < nc) step(r);
+#pragma unroll
+  for (int t = 0; t < NBT; ++t) {
+    float v = ss[t];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    rinv[t] = 1.0f / sqrtf(v / (float)d + eps);
+  }
+}
+
+// f32_rows for a workgroup of NW waves that share their 16 NBT tokens: the
+// tokens' rows pass through LDS in K-steps of 64 (256 contiguous bytes per row and
+// load), double buffered, loaded two steps ahead; weight rows stay direct.  Same
+// chains, same values.  A direct load of 16 rows x 64 bytes occupies the load path
+// for about 43 cycles, as long as a third of the chunk's matrix work: with every
+// wave loading its own tokens that path bound the kernels.
+// row(i): token i's row (any readable row past the end).  lds: 2 x 16 NBT x
+// kF32Ld floats; a barrier must follow before its next use.
+constexpr int kF32Ld = kKT + 4;
+template <int NBF, int NBT, int NW, class Row>
+__device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF], const Row& row, const float* gam, int d,
+                                                float eps, float* lds, f32x4_t (&acc)[NBF][NBT],
+                                                float (&rinv)[NBT]) {
+  constexpr int CPT = 16 * NBT * 16 / (64 * NW);  // 16-byte chunks per thread and step
+  static_assert(CPT >= 1 && CPT * 64 * NW == 16 * NBT * 16, "staging shape");
+  constexpr int SLOT = 16 * NBT * kF32Ld;
+  const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, lg = lane >> 4;
+  const int nsteps = d / kKT;
+  const float* hp[CPT];
+  int ho[CPT];
+#pragma unroll
+  for (int r = 0; r < CPT; ++r) {
+    const int i = tid + 64 * NW * r;
+    hp[r] = row(i >> 4) + 4 * (i & 15);
+    ho[r] = (i >> 4) * kF32Ld + 4 * (i & 15);
+  }
+  f32x4_t H[2][CPT], A[4][NBF], G[4];
+  float ss[NBT];
+#pragma unroll
+  for (int t = 0; t < NBT; ++t) {
+    ss[t] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) acc[i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  auto load_h = [&](int set, int s) {
+#pragma unroll
+    for (int r = 0; r < CPT; ++r) H[set][r] = *reinterpret_cast<const f32x4_t*>(hp[r] + kKT * min(s, nsteps - 1));
+  };
+  auto put_h = [&](int set, int slot) {
+#pragma unroll
+    for (int r = 0; r < CPT; ++r) *reinterpret_cast<f32x4_t*>(lds + slot * SLOT + ho[r]) = H[set][r];
+  };
+  auto load_w = [&](int c, int s) {
+    const int o = kKT * min(s, nsteps - 1) + 16 * c;
+    G[c] = *reinterpret_cast<const f32x4_t*>(gam + o);
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) A[c][i] = *reinterpret_cast<const f32x4_t*>(wrow[i] + o);
+  };
+  auto barrier = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS accesses are done
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // step s (P = s % 2): rows of step s + 1 into the other slot, those of s + 3
+  // requested, then the step's four chunks
+  auto iter = [&](auto pc, int s) {
+    constexpr int P = decltype(pc)::value;
+    put_h(P ^ 1, P ^ 1);
+    load_h(P ^ 1, s + 3);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      f32x4_t x[NBT];
+#pragma unroll
+      for (int t = 0; t < NBT; ++t)
+        x[t] = *reinterpret_cast<const f32x4_t*>(lds + P * SLOT + (16 * t + lq) * kF32Ld + 16 * c + 4 * lg);
+#pragma unroll
+      for (int t = 0; t < NBT; ++t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss[t] = fmaf(x[t][e], x[t][e], ss[t]);
+        x[t] = x[t] * G[c];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < NBF; ++i)
+#pragma unroll
+          for (int t = 0; t < NBT; ++t)
+            acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[c][i][e], x[t][e], acc[i][t], 0, 0, 0);
+      load_w(c, s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    barrier();
+  };
+  load_h(0, 0);
+  load_h(1, 1);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) load_w(c, 0);
+  put_h(0, 0);
+  load_h(0, 2);
+  barrier();
+  int s = 0;
+  for (; s + 2 <= nsteps; s += 2) {
+    iter(IC<0>{}, s);
+    iter(IC<1>{}, s + 1);
+  }
+  if (s < nsteps) iter(IC<0>{}, s);
 #pragma unroll
   for (int t = 0; t < NBT; ++t) {
     float v = ss[t];
@@ -907,7 +1023,7 @@ __device__ __forceinline__ float4 f32_finish(const f32x4_t& a, float ri, int rop
 // The fused kernel's fp32 tile: 8 waves, wave w owns the 16-row blocks w, w + 8,
 // .. of the 2 * HD rows (K rows, then V rows) for all MT tokens of the tile,
 // which go to the LDS tile [MT][K | V].  MFMA-bound on its CU (64 tokens of
-// head_dim 64 at d 576: 37k cycles).
+// head_dim 64 at d 576: 37k cycles; 52 us per call with direct token loads).
 template <int HD, int MT>
 struct F32Tile {
   static constexpr int NT = kNtTile;
@@ -918,26 +1034,25 @@ struct F32Tile {
   // h_tile: the tile's n <= MT rows (tokens past n read row 0 and get K = V = 0).
   // setup(): the caller's LDS writes of pos and rev.
   template <class Setup>
+  // hst: 2 x MT x kF32Ld floats of LDS (may alias kv).
   static __device__ __forceinline__ void run(const float* h_tile, int n, const float* gamma, int d, float eps,
-                                             const Half (&halves)[2], const int* pos, const double* rev, float* kv,
+                                             const Half (&halves)[2], float* hst, const int* pos, const double* rev, float* kv,
                                              const Setup& setup) {
     const int lane = threadIdx.x & 63, w = wave_id();
     const int lq = lane & 15, lg = lane >> 4;
     const float* const w0 = static_cast<const float*>(halves[0].w);
     const float* const w1 = static_cast<const float*>(halves[1].w);
     const float* wrow[NBF];
-    const float* hrow[NBT];
 #pragma unroll
     for (int i = 0; i < NBF; ++i) {
       const int r = 16 * (w + 8 * i) + lq;
       wrow[i] = (r < HD ? w0 + (size_t)r * d : w1 + (size_t)(r - HD) * d) + 4 * lg;
     }
-#pragma unroll
-    for (int t = 0; t < NBT; ++t) hrow[t] = h_tile + (size_t)(16 * t + lq < n ? 16 * t + lq : 0) * d + 4 * lg;
     setup();
     f32x4_t acc[NBF][NBT];
     float rinv[NBT];
-    f32_rows<NBF, NBT, NBF == 1 ? 4 : 3>(wrow, hrow, gamma + 4 * lg, d, eps, acc, rinv);
+    f32_rows_staged<NBF, NBT, NT / 64>(wrow, [&](int t) { return h_tile + (size_t)(t < n ? t : 0) * d; },
+                                       gamma + 4 * lg, d, eps, hst, acc, rinv);
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < NBT; ++t) {

@@ -130,7 +130,8 @@ __global__ __launch_bounds__(kNtTile, 1) void proj_kernel(ProjArgs a, int per_xc
 // ------------------------------------------------------------------ fp32 projections
 
 // fp32 q / K / V of B * T token rows: one wave per 16 weight rows x 16 NBT
-// tokens (f32_rows), its results stored straight to global memory.  Row blocks
+// tokens (f32_rows, or f32_rows_staged where NW waves share the tokens), its
+// results stored straight to global memory.  Row blocks
 // in order: the K rows of n_kv_units heads, their V rows, then the n_q query
 // heads' rows (q != 0).  grid: (row blocks / NW) * token blocks; a workgroup's
 // NW waves share its tokens.  At one token the launch is a chain of d / 4
@@ -149,7 +150,6 @@ __global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb)
   const float* wm = static_cast<const float*>(mat == 1 ? a.w_k : mat == 2 ? a.w_v : a.w_q);
   const float* const wrow[1] = {wm + (size_t)(r0 + lq) * a.d + 4 * lg};
   const long long ntok = (long long)a.B * a.T, n0 = (long long)tb * 16 * NBT;
-  const float* hrow[NBT];
   int b[NBT], t[NBT];
   bool ok[NBT];
 #pragma unroll
@@ -159,11 +159,24 @@ __global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb)
     const long long nn = ok[k] ? n : n0;  // tokens past the end repeat a row and are not stored
     b[k] = (int)(nn / a.T);
     t[k] = (int)(nn - (long long)b[k] * a.T);
-    hrow[k] = static_cast<const float*>(a.h) + ((size_t)b[k] * a.h_ld + t[k]) * a.d + 4 * lg;
   }
   f32x4_t acc[1][NBT];
   float rinv[NBT];
-  f32_rows<1, NBT, R>(wrow, hrow, static_cast<const float*>(a.gamma) + 4 * lg, a.d, a.eps, acc, rinv);
+  const float* gam = static_cast<const float*>(a.gamma) + 4 * lg;
+  if constexpr (NW == 1) {
+    const float* hrow[NBT];
+#pragma unroll
+    for (int k = 0; k < NBT; ++k) hrow[k] = static_cast<const float*>(a.h) + ((size_t)b[k] * a.h_ld + t[k]) * a.d + 4 * lg;
+    f32_rows<1, NBT, R>(wrow, hrow, gam, a.d, a.eps, acc, rinv);
+  } else {
+    __shared__ __align__(16) float hst[2 * 16 * NBT * kF32Ld];
+    auto row = [&](int i) {
+      const long long n = n0 + i < ntok ? n0 + i : n0;
+      const int rb = (int)(n / a.T);
+      return static_cast<const float*>(a.h) + ((size_t)rb * a.h_ld + (int)(n - (long long)rb * a.T)) * a.d;
+    };
+    f32_rows_staged<1, NBT, NW>(wrow, row, gam, a.d, a.eps, hst, acc, rinv);
+  }
   const int head = r0 / HD, f0 = r0 % HD + 4 * lg;
 #pragma unroll
   for (int k = 0; k < NBT; ++k) {
@@ -694,7 +707,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs& a, int per_xcd, int 
                                           hst, rinv, pos, rev, kv, setup);
     } else {
       F32Tile<HD, MT>::run(static_cast<const float*>(a.h) + ((size_t)b * a.h_ld + t0) * a.d, n,
-                           static_cast<const float*>(a.gamma), a.d, a.eps, halves, pos, rev, kv, setup);
+                           static_cast<const float*>(a.gamma), a.d, a.eps, halves, hst, pos, rev, kv, setup);
     }
     __syncthreads();
     if (a.dbg_k != nullptr) {
@@ -1453,7 +1466,7 @@ static hipError_t f32_proj_t(const ProjArgs& a, int n_units, hipStream_t st) {
   const int rows = 2 * a.n_kv_units * HD + (n_units > a.n_kv_units ? a.n_q * HD : 0);
   const long long waves = (long long)(rows / 16) * (((long long)a.B * a.T + 15) / 16);
   if (waves <= 1024) return f32_proj_nt<HD, 1, 1, 12>(a, rows, st);
-  return f32_proj_nt<HD, 2, 4, 6>(a, rows, st);
+  return f32_proj_nt<HD, 2, 4, 0>(a, rows, st);
 }
 
 template <int HD, int L>
