@@ -672,8 +672,8 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
   a.ws_acc = ws_acc_ptr(shape, B, ws);
   a.ws_ml = ws_ml_ptr(shape, B, S, ws);
   a.ws_done = ws_done_ptr(ws);
+  a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ws_ctr_bytes(shape, B));
   if (split) {
-    a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ws_ctr_bytes(shape, B));
     a.xch = reinterpret_cast<float*>(static_cast<char*>(ws) + ws_total(shape, B, S));
     a.xf = kvd::split_xf(shape->n_q_heads / shape->n_kv_heads, plan.mt);
   }

@@ -908,16 +908,17 @@ __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const 
 // chains, same values.  A direct load of 16 rows x 64 bytes occupies the load path
 // for about 43 cycles, as long as a third of the chunk's matrix work: with every
 // wave loading its own tokens that path bound the kernels.
-// row(i): token i's row (any readable row past the end).  lds: 2 x 16 NBT x
+// A wave takes the 16 NBT of the NTOK staged tokens that start at tok0.
+// row(i): token i's row (any readable row past the end).  lds: 2 x NTOK x
 // kF32Ld floats; a barrier must follow before its next use.
 constexpr int kF32Ld = kKT + 4;
-template <int NBF, int NBT, int NW, class Row>
+template <int NBF, int NBT, int NW, int NTOK, class Row>
 __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF], const Row& row, const float* gam, int d,
-                                                float eps, float* lds, f32x4_t (&acc)[NBF][NBT],
+                                                float eps, float* lds, int tok0, f32x4_t (&acc)[NBF][NBT],
                                                 float (&rinv)[NBT]) {
-  constexpr int CPT = 16 * NBT * 16 / (64 * NW);  // 16-byte chunks per thread and step
-  static_assert(CPT >= 1 && CPT * 64 * NW == 16 * NBT * 16, "staging shape");
-  constexpr int SLOT = 16 * NBT * kF32Ld;
+  constexpr int CPT = NTOK * 16 / (64 * NW);  // 16-byte chunks per thread and step
+  static_assert(CPT >= 1 && CPT * 64 * NW == NTOK * 16, "staging shape");
+  constexpr int SLOT = NTOK * kF32Ld;
   const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, lg = lane >> 4;
   const int nsteps = d / kKT;
   const float* hp[CPT];
@@ -969,7 +970,7 @@ __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF],
       f32x4_t x[NBT];
 #pragma unroll
       for (int t = 0; t < NBT; ++t)
-        x[t] = *reinterpret_cast<const f32x4_t*>(lds + P * SLOT + (16 * t + lq) * kF32Ld + 16 * c + 4 * lg);
+        x[t] = *reinterpret_cast<const f32x4_t*>(lds + P * SLOT + (tok0 + 16 * t + lq) * kF32Ld + 16 * c + 4 * lg);
 #pragma unroll
       for (int t = 0; t < NBT; ++t) {
 #pragma unroll
@@ -1020,48 +1021,54 @@ __device__ __forceinline__ float4 f32_finish(const f32x4_t& a, float ri, int rop
   return make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// The fused kernel's fp32 tile: 8 waves, wave w owns the 16-row blocks w, w + 8,
-// .. of the 2 * HD rows (K rows, then V rows) for all MT tokens of the tile,
-// which go to the LDS tile [MT][K | V].  MFMA-bound on its CU (64 tokens of
-// head_dim 64 at d 576: 37k cycles; 52 us per call with direct token loads).
-template <int HD, int MT>
+// The fused kernels' fp32 tile: 8 waves for MT tokens of the R = 2 * HD rows of
+// halves[0] (K) and halves[1] (V), or with SPLIT of the R = HD rows of halves[0].
+// Wave w owns the 16-row blocks w % WF, w % WF + WF, .. for its share of the
+// tokens; results go to the LDS tile [MT][KLD].  MFMA-bound on its CU (64 tokens
+// of head_dim 64, both halves, at d 576: 37k cycles; 52 us per call with direct
+// token loads, 34 staged).
+template <int HD, int MT, bool SPLIT = false, int KLDX = kv_ld<float>(HD)>
 struct F32Tile {
   static constexpr int NT = kNtTile;
-  static constexpr int NBF = 2 * HD / 16 / (NT / 64);
-  static constexpr int NBT = MT / 16;
-  static constexpr int KLD = kv_ld<float>(HD);
+  static constexpr int NB = (SPLIT ? HD : 2 * HD) / 16;
+  static constexpr int WF = NB < 8 ? NB : 8;
+  static constexpr int NBF = NB / WF;
+  static constexpr int NBT = MT / 16 * WF / 8;
+  static constexpr int KLD = KLDX;
+  static_assert(NBF * WF == NB && NBT >= 1, "wave layout");
 
-  // h_tile: the tile's n <= MT rows (tokens past n read row 0 and get K = V = 0).
+  // h_tile: the tile's n <= MT rows (tokens past n read row 0 and get zeros).
   // setup(): the caller's LDS writes of pos and rev.
-  template <class Setup>
   // hst: 2 x MT x kF32Ld floats of LDS (may alias kv).
+  template <class Setup>
   static __device__ __forceinline__ void run(const float* h_tile, int n, const float* gamma, int d, float eps,
-                                             const Half (&halves)[2], float* hst, const int* pos, const double* rev, float* kv,
-                                             const Setup& setup) {
+                                             const Half (&halves)[2], float* hst, const int* pos, const double* rev,
+                                             float* kv, const Setup& setup) {
     const int lane = threadIdx.x & 63, w = wave_id();
     const int lq = lane & 15, lg = lane >> 4;
+    const int wf = w % WF, tok0 = w / WF * 16 * NBT;
     const float* const w0 = static_cast<const float*>(halves[0].w);
     const float* const w1 = static_cast<const float*>(halves[1].w);
     const float* wrow[NBF];
 #pragma unroll
     for (int i = 0; i < NBF; ++i) {
-      const int r = 16 * (w + 8 * i) + lq;
+      const int r = 16 * (wf + WF * i) + lq;
       wrow[i] = (r < HD ? w0 + (size_t)r * d : w1 + (size_t)(r - HD) * d) + 4 * lg;
     }
     setup();
     f32x4_t acc[NBF][NBT];
     float rinv[NBT];
-    f32_rows_staged<NBF, NBT, NT / 64>(wrow, [&](int t) { return h_tile + (size_t)(t < n ? t : 0) * d; },
-                                       gamma + 4 * lg, d, eps, hst, acc, rinv);
+    f32_rows_staged<NBF, NBT, NT / 64, MT>(wrow, [&](int t) { return h_tile + (size_t)(t < n ? t : 0) * d; },
+                                           gamma + 4 * lg, d, eps, hst, tok0, acc, rinv);
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < NBT; ++t) {
-      const int tok = 16 * t + lq;
+      const int tok = tok0 + 16 * t + lq;
       const int p = pos[tok];
       const float ri = tok < n ? rinv[t] : 0.0f;
 #pragma unroll
       for (int i = 0; i < NBF; ++i) {
-        const int r = 16 * (w + 8 * i), half = r >= HD, f0 = r - half * HD + 4 * lg;
+        const int r = 16 * (wf + WF * i), half = r >= HD, f0 = r - half * HD + 4 * lg;
         *reinterpret_cast<float4*>(kv + (size_t)tok * KLD + half * HD + f0) =
             f32_finish(acc[i][t], ri, half ? halves[1].rope : halves[0].rope, p, rev, f0);
       }

@@ -54,6 +54,7 @@ constexpr int split_xf(int g, int mt) { return (g * (mt + 4) + 2 * g + 3) / 4 * 
 // this many CUs (half the chip): sliding-window layers and short contexts at
 // small batch, where each workgroup's K-loop over d_model sets the time.
 constexpr long long kSplit64MaxTiles = 128;
+constexpr int kF32SplitMaxTiles = 128;  // the fp32 roles: twice as many workgroups, at most one per CU
 constexpr int split_ld(int hd) { return hd + 8; }
 // Prefill / recompute (kvd_recompute_kv, the block forward's projections) runs
 // on the split engine for bf16 at head_dim 256, and at head_dim 128 when its
