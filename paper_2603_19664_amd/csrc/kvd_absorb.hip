@@ -19,6 +19,15 @@ namespace kvd {
 
 // ------------------------------------------------------------------ scores
 
+// Element of the scores of (b, token t, query head h): per 32-token block, the 4
+// tokens 8 lg + 4 half .. of every head in one run, so that a wave of the absorb
+// kernel reads a block in contiguous pieces (with a row per head its strided
+// 16-byte reads took as long as the residuals': 13.1 us at B = 1 x 4096 tokens).
+__device__ __forceinline__ size_t score_at(const AbsorbArgs& a, int b, int t, int h) {
+  const int e = t & 31;
+  return ((size_t)b * a.Tp + (t & ~31)) * a.n_q + (((e & 4) + (e >> 3)) * a.n_q + h) * 4 + (e & 3);
+}
+
 // One workgroup: RW rows of W_k (RW / HD heads) for MT tokens on WideTile's
 // K-loop (MFMA-bound at large grids: B = 16 x 2560 tokens in 217 us, 1.0 PFLOP/s;
 // at B = 1 x 4096 the 40 K-steps of one round, 28 us), then per token the dot product of the rotated
@@ -132,8 +141,7 @@ __global__ __launch_bounds__(Tile::NT, 1) void score_kernel(AbsorbArgs a, int pe
             float s = 0.0f;
 #pragma unroll
             for (int k = 0; k < BPH; ++k) s += red[((size_t)(hd * BPH + k) * kScoreHeads + hq) * MT + tok];
-            a.scores[((size_t)b * a.n_q + (size_t)(j0 + hd) * g + h0 + hq) * a.Tp + t0 + tok] =
-                tok < n ? s : -INFINITY;
+            a.scores[score_at(a, b, t0 + tok, (j0 + hd) * g + h0 + hq)] = tok < n ? s : -INFINITY;
           }
           __syncthreads();
         }
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(64 * kAbsorbWaves, 2) void absorb_kernel(AbsorbArgs
   const int nblk = (nb - s + a.S - 1) / a.S;
   const int col = min(sl * kAbsorbCols + 8 * lq, a.d - 8);  // d is a multiple of 64: the last slice may be half empty
   const int head = min(PACK ? lq & 7 : lq, a.n_q - 1);
-  const float* sp = a.scores + ((size_t)b * a.n_q + head) * a.Tp + 8 * lg;
+  const float* sp = a.scores + (size_t)b * a.Tp * a.n_q + (lg * a.n_q + head) * 4;
   const float* rp = a.rinv + (size_t)b * a.Tp + 8 * lg;
   const uint16_t* hp = static_cast<const uint16_t*>(a.h) + (size_t)b * a.h_ld * a.d + col;
 
@@ -217,8 +225,8 @@ __global__ __launch_bounds__(64 * kAbsorbWaves, 2) void absorb_kernel(AbsorbArgs
   const int steps = (nblk - w + kAbsorbWaves - 1) / kAbsorbWaves;
   auto load = [&](int k, int i) {  // the wave's step i (steps past its last repeat it)
     const int t = kAbsorbBlock * (nb - 1 - ((w + kAbsorbWaves * min(i, steps - 1)) * a.S + s));
-    sv[k][0] = *reinterpret_cast<const float4*>(sp + t);
-    sv[k][1] = *reinterpret_cast<const float4*>(sp + t + 4);
+    sv[k][0] = *reinterpret_cast<const float4*>(sp + (size_t)t * a.n_q);
+    sv[k][1] = *reinterpret_cast<const float4*>(sp + (size_t)t * a.n_q + 16 * a.n_q);
     rv[k][0] = *reinterpret_cast<const float4*>(rp + t);
     rv[k][1] = *reinterpret_cast<const float4*>(rp + t + 4);
 #pragma unroll

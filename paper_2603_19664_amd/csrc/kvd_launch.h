@@ -65,7 +65,7 @@ struct FusedArgs {
 // loop (bf16, head_dim 256): V is linear in the residual, so
 //   sum_t p_t V_t = W_v sum_t p_t r_t (gamma * h_t),   r_t = 1 / rms(h_t),
 // and only the keys are recomputed per token.  Three launches:
-//   score_kernel   scores[b][h][t] = q_h . K_t (scaled into the log2 domain) and r_t;
+//   score_kernel   scores of (b, h, t): q_h . K_t (scaled into the log2 domain) and r_t;
 //   absorb_kernel  per (b, range s of the tokens, 128 columns of h): u[b][s][h] =
 //                  sum_t p_t r_t h_t and the range's (max, sum) in uml; the stored
 //                  tail's 64-row tiles attended into (tacc, tml) beside it;
@@ -81,7 +81,7 @@ struct AbsorbArgs {
   const void* tk;
   const void* tv;
   int tail_t_cap, tail_t_off, T_tail;
-  float* scores;  // [B][n_q][Tp]
+  float* scores;  // [B][Tp / 32][8][n_q][4] (score_at)
   float* rinv;    // [B][Tp]
   float* u;       // S > 1: [B][slices][S] x (sums [n_q][128], (max, sum) [n_q][2])
   uint16_t* uh;   // [B][n_q][2][d]: gamma * the merged sums as two bf16 parts
