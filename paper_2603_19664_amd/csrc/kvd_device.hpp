@@ -832,23 +832,30 @@ struct WideTile {
 // sums): a wave owns NBF blocks of 16 weight rows (A) and NBT blocks of 16 tokens
 // (B).  Both operands come straight from global memory, 16 bytes per lane: lane
 // group lg = lane / 16 holds k = 16 c + 4 lg .. + 3 of its row, and MFMA e of
-// chunk c takes element e of every lane, so an element's chain runs over d in
-// the order k = 16 c + 4 (0..3) + e.  Every fp32 producer of q, K and V (any
-// NBF, NBT) has this one chain, hence bit-identical values.  The sum of squares
+// chunk c takes element e of every lane.  An element has CH chains over d (CH =
+// f32_chains(head_dim)), chain e % CH in the order k = 16 c + 4 (0..3) + e, added
+// at the end: two halve the length of a rounded sum (2-norm error against 64 bits
+// 4.4e-7 with one chain, 3.2e-7 with two, at d 576; same time).  Every fp32
+// producer of q, K and V of a head_dim (any NBF, NBT) has these chains, hence
+// bit-identical values.  The sum of squares
 // of a token is four chains (one per lane group, in k order) added by a fixed
 // xor tree; each wave keeps its own, so nothing passes through LDS.
 // R chunks are in flight.
-template <int NBF, int NBT, int R>
+constexpr int f32_chains(int hd) { return hd == 256 ? 1 : 2; }  // two sets of accumulators spill at head_dim 256
+template <int NBF, int NBT, int R, int CH>
 __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const float* const (&hrow)[NBT],
                                          const float* gam, int d, float eps, f32x4_t (&acc)[NBF][NBT],
                                          float (&rinv)[NBT]) {
   const int nc = d / 16;
+  f32x4_t chain[CH][NBF][NBT];
   float ss[NBT];
 #pragma unroll
   for (int t = 0; t < NBT; ++t) {
     ss[t] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NBF; ++i) acc[i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < NBF; ++i)
+#pragma unroll
+      for (int k = 0; k < CH; ++k) chain[k][i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
   }
   f32x4_t A[R][NBF], B[R][NBT], G[R];
   auto load = [&](int slot, int c) {
@@ -873,7 +880,8 @@ __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const 
       for (int i = 0; i < NBF; ++i)
 #pragma unroll
         for (int t = 0; t < NBT; ++t)
-          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][i][e], x[t][e], acc[i][t], 0, 0, 0);
+          chain[e % CH][i][t] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(A[r][i][e], x[t][e], chain[e % CH][i][t], 0, 0, 0);
   };
 #pragma unroll
   for (int r = 0; r < R - 1; ++r) load(r, r);
@@ -895,6 +903,11 @@ __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const 
     if (c0 + r < nc) step(r);
 #pragma unroll
   for (int t = 0; t < NBT; ++t) {
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) {
+      acc[i][t] = chain[0][i][t];
+      if constexpr (CH == 2) acc[i][t] += chain[1][i][t];
+    }
     float v = ss[t];
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
@@ -912,7 +925,7 @@ __device__ __forceinline__ void f32_rows(const float* const (&wrow)[NBF], const 
 // row(i): token i's row (any readable row past the end).  lds: 2 x NTOK x
 // kF32Ld floats; a barrier must follow before its next use.
 constexpr int kF32Ld = kKT + 4;
-template <int NBF, int NBT, int NW, int NTOK, class Row>
+template <int NBF, int NBT, int NW, int NTOK, int CH, class Row>
 __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF], const Row& row, const float* gam, int d,
                                                 float eps, float* lds, int tok0, f32x4_t (&acc)[NBF][NBT],
                                                 float (&rinv)[NBT]) {
@@ -930,12 +943,15 @@ __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF],
     ho[r] = (i >> 4) * kF32Ld + 4 * (i & 15);
   }
   f32x4_t H[2][CPT], A[4][NBF], G[4];
+  f32x4_t chain[CH][NBF][NBT];
   float ss[NBT];
 #pragma unroll
   for (int t = 0; t < NBT; ++t) {
     ss[t] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NBF; ++i) acc[i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < NBF; ++i)
+#pragma unroll
+      for (int k = 0; k < CH; ++k) chain[k][i][t] = {0.0f, 0.0f, 0.0f, 0.0f};
   }
   auto load_h = [&](int set, int s) {
 #pragma unroll
@@ -983,7 +999,8 @@ __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF],
         for (int i = 0; i < NBF; ++i)
 #pragma unroll
           for (int t = 0; t < NBT; ++t)
-            acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[c][i][e], x[t][e], acc[i][t], 0, 0, 0);
+            chain[e % CH][i][t] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(A[c][i][e], x[t][e], chain[e % CH][i][t], 0, 0, 0);
       load_w(c, s + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1004,6 +1021,11 @@ __device__ __forceinline__ void f32_rows_staged(const float* const (&wrow)[NBF],
   if (s < nsteps) iter(IC<0>{}, s);
 #pragma unroll
   for (int t = 0; t < NBT; ++t) {
+#pragma unroll
+    for (int i = 0; i < NBF; ++i) {
+      acc[i][t] = chain[0][i][t];
+      if constexpr (CH == 2) acc[i][t] += chain[1][i][t];
+    }
     float v = ss[t];
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
@@ -1058,7 +1080,7 @@ struct F32Tile {
     setup();
     f32x4_t acc[NBF][NBT];
     float rinv[NBT];
-    f32_rows_staged<NBF, NBT, NT / 64, MT>(wrow, [&](int t) { return h_tile + (size_t)(t < n ? t : 0) * d; },
+    f32_rows_staged<NBF, NBT, NT / 64, MT, f32_chains(HD)>(wrow, [&](int t) { return h_tile + (size_t)(t < n ? t : 0) * d; },
                                            gamma + 4 * lg, d, eps, hst, tok0, acc, rinv);
     __syncthreads();
 #pragma unroll

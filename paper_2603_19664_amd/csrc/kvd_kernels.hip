@@ -134,8 +134,8 @@ __global__ __launch_bounds__(kNtTile, 1) void proj_kernel(ProjArgs a, int per_xc
 // results stored straight to global memory.  Row blocks
 // in order: the K rows of n_kv_units heads, their V rows, then the n_q query
 // heads' rows (q != 0).  grid: (row blocks / NW) * token blocks; a workgroup's
-// NW waves share its tokens.  At one token the launch is a chain of d / 4
-// dependent MFMAs (about 3 us at d 576).
+// NW waves share its tokens.  At one token the launch is a chain of
+// dependent MFMAs.
 template <int HD, int NBT, int NW, int R>
 __global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb) {
   __shared__ double rev[HD / 2];
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb)
     const float* hrow[NBT];
 #pragma unroll
     for (int k = 0; k < NBT; ++k) hrow[k] = static_cast<const float*>(a.h) + ((size_t)b[k] * a.h_ld + t[k]) * a.d + 4 * lg;
-    f32_rows<1, NBT, R>(wrow, hrow, gam, a.d, a.eps, acc, rinv);
+    f32_rows<1, NBT, R, f32_chains(HD)>(wrow, hrow, gam, a.d, a.eps, acc, rinv);
   } else {
     __shared__ __align__(16) float hst[2 * 16 * NBT * kF32Ld];
     auto row = [&](int i) {
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(64 * NW) void f32_proj_kernel(ProjArgs a, int n_tb)
       const int rb = (int)(n / a.T);
       return static_cast<const float*>(a.h) + ((size_t)rb * a.h_ld + (int)(n - (long long)rb * a.T)) * a.d;
     };
-    f32_rows_staged<1, NBT, NW, 16 * NBT>(wrow, row, gam, a.d, a.eps, hst, 0, acc, rinv);
+    f32_rows_staged<1, NBT, NW, 16 * NBT, f32_chains(HD)>(wrow, row, gam, a.d, a.eps, hst, 0, acc, rinv);
   }
   const int head = r0 / HD, f0 = r0 % HD + 4 * lg;
 #pragma unroll
