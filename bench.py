@@ -374,7 +374,7 @@ def main():
                    "step": "per layer: kvd_project_qkv + kvd_fused_recompute_attn (split-K merge in-kernel)",
                    "launch": "the K timed steps captured once as a HIP graph and replayed"},
         "eager_ms_per_step_with_events": ms_step_events,
-        "roofline": {"bound": "mfma", "kernel": "fused_kernel<bf16,256,64>", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": "kvd_fused_recompute_attn (score, absorb, vproj)", "achieved": achieved,
                      "peak": MI355X_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MI355X_BF16_PEAK_TFLOPS,
                      "traffic": traffic, "flops_per_launch": flops, "us_per_launch": 1e3 * fused_ms},
         "per_op_us": per_op,

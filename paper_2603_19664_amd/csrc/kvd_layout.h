@@ -169,7 +169,7 @@ __attribute__((always_inline)) constexpr AttnLds attn_lds(size_t base, int g, in
 // LDS layout of the recompute engine: staged h-bar tiles, the K/V tile (aliases
 // the staging buffers), per-token 1/rms and positions, and the RoPE frequency
 // table.  bf16: a ring of kDepth K-steps of mt tokens x kKT in MFMA B-fragment
-// order; fp32: one [mt][h_ld] tile.
+// order; fp32: two K-steps of [mt][h_ld].
 struct ProjLds {
   size_t hst, kv, rinv, pos, rev, end;
 };
