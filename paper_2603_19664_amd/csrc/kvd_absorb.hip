@@ -44,7 +44,10 @@ __global__ __launch_bounds__(Tile::NT, 1) void score_kernel(AbsorbArgs a, int pe
   const int C = (a.T + MT - 1) / MT;
   const int n_rg = a.n_kv * HD / RW;
   const unsigned item = (blockIdx.x % kXcds) * (unsigned)per_xcd + blockIdx.x / kXcds;
-  if (item >= (unsigned)n_rg * (unsigned)a.B * (unsigned)C) return;
+  const unsigned n_items = (unsigned)n_rg * (unsigned)a.B * (unsigned)C;
+  if (item >= n_items) return;
+  // the next kernel's arrival counters start at zero whatever the workspace held
+  for (size_t i = (size_t)item * NT + tid; i < (size_t)a.n_done; i += (size_t)n_items * NT) a.done[i] = 0u;
   // items as in the fused kernels: groups of hg row groups of one sequence,
   // token tiles in order, row groups alternating
   const int hg_log2 = __builtin_ctz((unsigned)hg);
@@ -388,12 +391,11 @@ __global__ __launch_bounds__(64 * kAbsorbWaves, 2) void absorb_kernel(AbsorbArgs
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's partial is written
   __syncthreads();
-  unsigned* ctr = a.done + (size_t)b * a.done_ld + sl;
+  unsigned* ctr = a.done + (size_t)b * n_sl + sl;
   unsigned* bc = reinterpret_cast<unsigned*>(red);
   if (tid == 0) *bc = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (*bc != (unsigned)a.S - 1) return;
-  if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   float* ws = red + 4;  // [n_q][S] weights
   if (tid < a.n_q) {
     float mk[kAbsorbMaxRanges], lk[kAbsorbMaxRanges];

@@ -511,8 +511,8 @@ kvd_status check_fused_args(const kvd_attn_shape* shape, const void* q, const vo
 // workspace's counters, fits the workspace of the tiled engines
 // (kvd_workspace_bytes), so no call needs a larger one.
 struct AbsorbPlan {
-  int32_t tile, Tp, S, n_tail;
-  size_t scores, rinv, u, uh, uml, tacc, tml, end;  // byte offsets from the workspace's start
+  int32_t tile, Tp, S, n_tail, n_done;
+  size_t scores, rinv, u, uh, uml, tacc, tml, done, end;  // byte offsets from the workspace's start
 };
 
 // kvd_workspace_bytes of KVD_OP_FUSED: enough for any tiling, so that the size
@@ -529,16 +529,18 @@ size_t fused_ws_bytes(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t
 // Lays the plan out for S ranges.
 void absorb_layout(const kvd_attn_shape* s, int32_t B, int32_t S, AbsorbPlan* p) {
   const size_t bq = (size_t)B * s->n_q_heads;
+  const int32_t slices = ceil_div(s->d_model, kvd::kAbsorbCols);
   p->S = S;
+  p->n_done = S > 1 ? B * slices : 0;
   p->scores = ws_done_bytes(s, B);
   p->rinv = p->scores + kvd::align_up(4 * bq * p->Tp, 256);
   p->u = p->rinv + kvd::align_up((size_t)4 * B * p->Tp, 256);
-  p->uh = p->u + (p->S > 1 ? kvd::align_up(4 * bq * p->S * ceil_div(s->d_model, kvd::kAbsorbCols) *
-                                               (kvd::kAbsorbCols + 2), 256) : 0);
+  p->uh = p->u + (S > 1 ? kvd::align_up(4 * bq * S * slices * (kvd::kAbsorbCols + 2), 256) : 0);
   p->uml = p->uh + kvd::align_up(4 * bq * s->d_model, 256);
   p->tacc = p->uml + kvd::align_up(8 * bq, 256);
   p->tml = p->tacc + kvd::align_up(4 * bq * p->n_tail * s->head_dim, 256);
-  p->end = p->tml + kvd::align_up(8 * bq * p->n_tail, 256);
+  p->done = p->tml + kvd::align_up(8 * bq * p->n_tail, 256);
+  p->end = p->done + kvd::align_up((size_t)4 * p->n_done, 256);
 }
 
 // True and the plan when the call takes the value-absorbed path: automatic mode,
@@ -576,13 +578,10 @@ bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_ta
   const int64_t slices = ceil_div(s->d_model, kvd::kAbsorbCols);
   if (slices * B * kvd::kAbsorbMaxRanges + (int64_t)p->n_tail * s->n_kv_heads * B > INT32_MAX) return false;
   // ranges of a sequence: enough for about kAbsorbMinWgs workgroups, each at least
-  // 256 tokens, as far as the scratch and the arrival counters (two per
-  // completion word) allow
-  // (and the static scratch, so that the call without a workspace runs the same
-  // kernels)
+  // 256 tokens, as far as the scratch allows (and the static scratch, so that the
+  // call without a workspace runs the same kernels)
   const size_t limit = std::min({ws_bytes, fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes});
-  int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
-  if (slices > 2 * kvd::kSplitBitWords * s->n_kv_heads) want = 1;
+  const int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
   for (int32_t S = want; S >= 1; --S) {
     if (S > 1 && T_rec / S < 256) continue;
     absorb_layout(s, B, S, p);
@@ -621,9 +620,8 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
     a.u = reinterpret_cast<float*>(base + ap.u);
     a.uml = reinterpret_cast<float*>(base + ap.uml);
     a.uh = reinterpret_cast<uint16_t*>(base + ap.uh);
-    // the arrival counters live in the completion words: two per 64-bit word
-    a.done = reinterpret_cast<unsigned*>(base + ws_ctr_bytes(shape, B));
-    a.done_ld = 2 * kvd::kSplitBitWords * shape->n_kv_heads;
+    a.done = reinterpret_cast<unsigned*>(base + ap.done);
+    a.n_done = ap.n_done;
     a.fold = shape->w_layout == KVD_W_PACKED_GAMMA;
     a.tacc = reinterpret_cast<float*>(base + ap.tacc);
     a.tml = reinterpret_cast<float*>(base + ap.tml);

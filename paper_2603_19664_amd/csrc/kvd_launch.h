@@ -86,8 +86,8 @@ struct AbsorbArgs {
   float* u;       // S > 1: [B][slices][S] x (sums [n_q][128], (max, sum) [n_q][2])
   uint16_t* uh;   // [B][n_q][2][d]: gamma * the merged sums as two bf16 parts
   float* uml;     // [B][n_q][2]
-  unsigned* done; // S > 1: [B][done_ld] arrivals per slice (zero between calls)
-  int done_ld;
+  unsigned* done; // [n_done] = [B][slices] arrivals per slice, cleared by score_kernel (n_done = 0 when S == 1)
+  int n_done;
   int fold;       // gamma is folded into the weights
   float* tacc;    // [B][n_q][n_tail][hd]
   float* tml;     // [B][n_q][n_tail][2]

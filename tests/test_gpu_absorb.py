@@ -180,3 +180,22 @@ def test_absorbed_under_capture():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(_bits(out), _bits(ref))
+
+
+@pytest.mark.parametrize("B,T,d,n_q,n_kv", [(1, 3101, 1024, 8, 4), (3, 1025, 1216, 16, 4), (2, 6200, 2560, 8, 2)])
+def test_workspace_with_only_the_split_counters_zero(B, T, d, n_q, n_kv):
+    # kvd.h asks for zero split counters and nothing else: calls of several ranges on
+    # a workspace whose other bytes hold anything equal the call on a zeroed one,
+    # the first time and again
+    L = _layer(B, T, d, n_q, n_kv)
+    s = L.shape
+    q, (tk, tv), ref, _ = gpu_fused(L)
+    ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, 1)
+    n = -(-B * n_kv * 8 // 256) * 256
+    for fill in (0xFF, 0x01, 0x03):
+        ws[n:] = fill
+        for _ in range(2):
+            out = torch.empty_like(q)
+            kvd.kvd_fused_recompute_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, tk, tv, 1)
+            assert torch.equal(_bits(out), _bits(ref))
+        assert int(torch.count_nonzero(ws[:n])) == 0
