@@ -171,9 +171,9 @@ kvd_status kvd_project_q(const kvd_attn_shape* shape, const void* h_new, const v
  * same kernel (an atomic split counter in the workspace; no spin-waits).
  * ws (256-byte aligned) must hold kvd_workspace_bytes(shape, KVD_OP_DECODE_ATTN,
  * B, T, 0) bytes.  Workspace contract: its first bytes hold split counters
- * ([B][n_kv_heads] uint64, padded to 256 bytes) that must be zero before the
- * first call that uses them (allocate the workspace zero-filled once); every
- * call leaves them zero.  The rest of the workspace is overwritten.  Their
+ * ([B][n_kv_heads] uint64, padded to 256 bytes, the padding included) that
+ * must be zero before the first call that uses them (allocate the workspace
+ * zero-filled once); every call leaves them zero.  The rest of the workspace is overwritten.  Their
  * place depends on B only, so attention calls of any key count and op (decode,
  * cached, fused) with the same B can share one workspace sized for the largest
  * of them, as a decode loop whose context grows does.  Calls sharing one
@@ -226,7 +226,10 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  *     the first has published the probabilities through the workspace, the
  *     P V products.  The second waits for the first with a bounded wait
  *     (about 0.1 s); past it that split's partial is NaN, so out shows it;
- *   - 64-token tiles of K and V rows otherwise.
+ *   - 64-token tiles of K and V rows otherwise.  fp32 calls of at most 128 of
+ *     them with out != NULL run a tile's K and V rows as two workgroups, like
+ *     the split engine and bit-identical to the tiles (with the same bounded
+ *     wait; past it out is NaN).
  * Before these, in automatic mode with out != NULL and no kv_debug: calls with
  * bf16, head_dim 256, at most 16 query heads, d_model >= 1024 and B *
  * n_kv_heads * ceil(T_rec / 64) >= 192 recompute keys only.  Values enter

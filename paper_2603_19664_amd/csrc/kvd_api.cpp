@@ -252,6 +252,19 @@ size_t ws_xch_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
 size_t ws_plan_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
   return ws_total(s, B, p.S) + (is_split(p) ? ws_xch_bytes(s, B, p) : 0);
 }
+// Place of the split engines' completion flags for n_rec chunks per sequence
+// (RoleFlag): the split counters themselves, or words in the rest of their
+// 256-byte padded block, which the caller zeroes with them.  Every call of at most
+// kF32SplitMaxTiles chunks has one: more than kRoleCtrChunks chunks then mean at
+// most three (sequence, KV head) pairs.
+struct RoleFlags {
+  int32_t words;   // per (sequence, KV head); 0: in the counters
+  size_t offset;   // of the words, from the workspace's start
+};
+RoleFlags role_flags(const kvd_attn_shape* s, int32_t B, int32_t n_rec) {
+  if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0};
+  return RoleFlags{ceil_div(n_rec, 64), (size_t)B * s->n_kv_heads * sizeof(uint64_t)};
+}
 float* ws_acc_ptr(const kvd_attn_shape* s, int32_t B, void* ws) {
   return reinterpret_cast<float*>(static_cast<char*>(ws) + ws_done_bytes(s, B));
 }
@@ -670,8 +683,13 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
   a.ws_acc = ws_acc_ptr(shape, B, ws);
   a.ws_ml = ws_ml_ptr(shape, B, S, ws);
   a.ws_done = ws_done_ptr(ws);
-  a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ws_ctr_bytes(shape, B));
+  if (shape->dtype == KVD_F32) {
+    const RoleFlags f = role_flags(shape, B, plan.n_rec);
+    a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + f.offset);
+    a.flag_words = f.words;
+  }
   if (split) {
+    a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ws_ctr_bytes(shape, B));
     a.xch = reinterpret_cast<float*>(static_cast<char*>(ws) + ws_total(shape, B, S));
     a.xf = kvd::split_xf(shape->n_q_heads / shape->n_kv_heads, plan.mt);
   }

@@ -1717,10 +1717,10 @@ __device__ __forceinline__ void combine_rows(const float* ws_acc, const float* w
 }
 
 // Split-K completion counter of (b, KV head j): one 64-bit word in the
-// workspace whose low 32 bits count the splits whose partials are written (the
-// high 32 bits are reserved and stay zero).  Every thread first waits for its own
-// device-scope partial stores to complete; then one thread adds `add` and the
-// value before the add is broadcast to the workgroup.
+// workspace whose low 32 bits count the arrivals (the high 32 bits are the split
+// engines' completion flags, RoleFlag; zero on the others).  Every thread first
+// waits for its own device-scope partial stores to complete; then one thread adds
+// `add` and the value before the add is broadcast to the workgroup.
 // No cache-wide write-back or invalidate is needed, so other workgroups that
 // stream weights through the same L2 keep them.
 __device__ __forceinline__ unsigned long long split_arrive(unsigned long long* ctr, unsigned long long add,
@@ -1742,5 +1742,40 @@ __device__ __forceinline__ bool split_complete(unsigned long long* ctr, unsigned
   if (last && threadIdx.x == 0) __hip_atomic_store(ctr, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return last;
 }
+
+// The split engines' handshake of a chunk: its K role sets the flag once its
+// probabilities are written, its V role waits for it.  flag_words == 0 (at most
+// kRoleCtrChunks chunks): bit 32 + c of the (b, KV head) split counter; otherwise
+// bit c % 64 of word c / 64 of the flag_words words at ws_bits.  Both roles
+// arrive at the counter (2 n_rec + n_tail arrivals in all), so the last arrival,
+// which clears counter and words, comes after every access to either, also when
+// a wait ran out: the V role then leaves kRoleTimedOut (bit 31) in the counter.
+constexpr unsigned long long kRoleTimedOut = 1ull << 31;
+struct RoleFlag {
+  unsigned long long* ctr;
+  unsigned long long* word;
+  unsigned long long bit;
+  __device__ __forceinline__ RoleFlag(unsigned long long* ctr_, unsigned long long* bits, int flag_words, size_t unit, int c)
+      : ctr(ctr_ + unit),
+        word(flag_words ? bits + unit * flag_words + (c >> 6) : ctr_ + unit),
+        bit(flag_words ? 1ull << (c & 63) : 1ull << (32 + c)) {}
+  // K role: publish what its threads have stored, and arrive.
+  __device__ __forceinline__ unsigned long long publish(unsigned long long* bcast) const {
+    if (word == ctr) return split_arrive(ctr, 1 + bit, bcast);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's stores are complete
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return split_arrive(ctr, 1, bcast);
+  }
+  // V role, one thread: bounded wait; false when it ran out.
+  __device__ __forceinline__ bool wait() const {
+    for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
+      if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) return true;
+      __builtin_amdgcn_s_sleep(2);
+    }
+    __hip_atomic_fetch_or(ctr, kRoleTimedOut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+};
 
 }  // namespace kvd

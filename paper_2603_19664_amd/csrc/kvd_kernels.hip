@@ -1070,17 +1070,17 @@ __global__ __launch_bounds__(split_nt(HD), 1) void fused_split_kernel(FusedArgs 
 // fp32 calls whose 64-token tiles would leave half the chip idle: the tile's K
 // and V rows run as two workgroups, each MFMA-bound on its CU for half as long
 // (SmolLM2-135M layer at 256 tokens: 12 tiles, 33.8 us per call with both halves
-// in one workgroup, 24.8 with two).  The protocol is the bf16 split engine's: the K
-// role takes the scores and softmax and publishes the probabilities, then sets
-// bit c of the (b, KV head) completion words; the V role waits for it (bounded),
-// takes P V, writes the partial, arrives and, if last, clears the words and
+// in one workgroup, 24.8 with two).  The K role takes the
+// scores and softmax and publishes the probabilities (RoleFlag); the V role waits
+// for them (bounded), takes P V and writes the partial; whoever arrives last
 // merges.  The probabilities travel in the chunk's own partial (64 keys <= HD
 // columns), which the V role then overwrites.  Same arithmetic as fused_kernel:
-// bit-identical results.  Grid in dispatch order, per (b, KV head): the stored
-// tail's tiles, then K role, V role of each chunk, so a K role is dispatched no
-// later than the V role that waits for it.
+// bit-identical results.  Grid: pair p (K role, then V role) on XCD p % 8, the
+// stored tail's tiles after the pairs.  An XCD starts its workgroups in order, so
+// a K role runs no later than the V role that waits for it, whatever else the
+// chip is doing, and depends on nothing itself.
 template <int HD>
-__global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a) {
+__global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a, int pair_slots) {
   extern __shared__ __align__(16) char lds[];
   constexpr int MT = kMtF32, NT = kNtTile;
   constexpr ProjLds PL = proj_lds<float>(HD, MT);
@@ -1088,17 +1088,23 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a) {
   static_assert(MT <= HD, "a chunk's probabilities fit its partial");
   const int tid = threadIdx.x;
   const int n_tail = a.S - a.n_rec;
-  const unsigned C = (unsigned)(n_tail + 2 * a.n_rec);
-  const unsigned gi = blockIdx.x / C;
-  const int ci = (int)(blockIdx.x - gi * C);
+  const unsigned units = (unsigned)a.n_kv * (unsigned)a.B;
+  const unsigned xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+  const bool tail = slot >= (unsigned)pair_slots;
+  const unsigned item = (tail ? slot - (unsigned)pair_slots : slot >> 1) * kXcds + xcd;
+  const unsigned per = (unsigned)(tail ? n_tail : a.n_rec);
+  if (item >= units * per) return;
+  const unsigned gi = item / per;
+  const int ci = (int)(item - gi * per);
   const int j = (int)(gi / (unsigned)a.B), b = (int)(gi - (unsigned)j * (unsigned)a.B);
   const int g = a.n_q / a.n_kv;
   const AttnLds AL = attn_lds(PL.end, g, HD, MT);
   float* kv = reinterpret_cast<float*>(lds + PL.kv);
-  int split = 0;
-  if (ci < n_tail) {  // a stored tile of up to 64 rows, as in fused_body
+  unsigned long long* bcast = reinterpret_cast<unsigned long long*>(lds + AL.ctr);
+  unsigned long long* ctr = a.ws_done + (size_t)b * a.n_kv + j;
+  unsigned long long before;
+  if (tail) {  // a stored tile of up to 64 rows, as in fused_body
     const int r0 = ci * kTile, nk = min(kTile, a.T_tail - r0);
-    split = a.n_rec + ci;
     load_q<float, HD, NT>(static_cast<const float*>(a.q), b, a.n_q, j, g, reinterpret_cast<float*>(lds + AL.q));
     int tr0 = a.tail_t_off + r0;
     tr0 -= tr0 >= a.tail_t_cap ? a.tail_t_cap : 0;
@@ -1106,11 +1112,11 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a) {
                                 a.tail_t_cap, tr0, nk, kv);
     __syncthreads();
     attend_tile<float, HD, NT, 1>(kv, nk, MT, g, lds, AL);
-    write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, split, tile_splits<float>(g));
+    write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, a.n_rec + ci, tile_splits<float>(g));
+    before = split_arrive(ctr, 1, bcast);
   } else {
-    const int c = (ci - n_tail) >> 1, role = (ci - n_tail) & 1;  // 0: K rows, 1: V rows
+    const int c = ci, role = (int)(slot & 1u);  // 0: K rows, 1: V rows
     const int t0 = c * MT, n = min(MT, a.T_rec - t0);
-    split = c;
     double* rev = reinterpret_cast<double*>(lds + PL.rev);
     int* pos = reinterpret_cast<int*>(lds + PL.pos);
     const TileSetup<float, HD, NT, true, false> su(static_cast<const float*>(a.q), b, a.n_q, j, g, a.gamma, a.d, a.rev);
@@ -1138,47 +1144,34 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a) {
     float* S = reinterpret_cast<float*>(lds + AL.s);
     float* ml = reinterpret_cast<float*>(lds + AL.ml);
     const size_t row0 = (size_t)b * a.n_q + (size_t)j * g;
-    unsigned long long* word = a.ws_bits + ((size_t)b * a.n_kv + j) * kSplitBitWords + (c >> 6);
+    const RoleFlag flag(a.ws_done, a.ws_bits, a.flag_words, (size_t)b * a.n_kv + j, c);
     if (role == 0) {
       attend_scores<float, HD, NT, 1, KLD>(kv, n, MT, g, lds, AL);
       for (int i = tid; i < g * MT; i += NT) store_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT, S[i]);
       if (tid < 2 * g) store_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1), ml[tid]);
-      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's stores are complete
+      before = flag.publish(bcast);
+    } else {
+      if (tid == 0) flag.wait();
       __syncthreads();
-      if (tid == 0) __hip_atomic_fetch_or(word, 1ull << (c & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int i = tid; i < g * MT; i += NT) S[i] = load_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT);
+      if (tid < 2 * g) ml[tid] = load_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1));
+      __syncthreads();
+      attend_pv<float, HD, NT, KLD>(kv, n, MT, g, lds, AL);
+      write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<float>(g));
+      before = split_arrive(ctr, 1, bcast);
+    }
+  }
+  if (split_complete(ctr, before & ~kRoleTimedOut, 1, n_tail + 2 * a.n_rec)) {
+    if (tid < a.flag_words)
+      __hip_atomic_store(a.ws_bits + ((size_t)b * a.n_kv + j) * a.flag_words + tid, 0ull, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    const size_t out0 = (size_t)b * a.n_q + (size_t)j * g;
+    if (before & kRoleTimedOut) {  // a late K role may have overwritten its V role's partial
+      for (int i = tid; i < g * HD; i += NT) static_cast<float*>(a.out)[out0 * HD + i] = __builtin_nanf("");
       return;
     }
-    int* flag = reinterpret_cast<int*>(lds + AL.ctr);
-    if (tid == 0) {
-      int ok = 0;
-      for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
-        if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (c & 63)) & 1ull) {
-          ok = 1;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      *flag = ok;
-    }
-    __syncthreads();
-    const bool ok = *flag != 0;
-    for (int i = tid; i < g * MT; i += NT) S[i] = load_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT);
-    if (tid < 2 * g) ml[tid] = ok ? load_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1)) : __builtin_nanf("");
-    __syncthreads();
-    attend_pv<float, HD, NT, KLD>(kv, n, MT, g, lds, AL);
-    write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<float>(g));
-  }
-  // every split arrives (also without out): the last one clears the completion
-  // words for the next call
-  unsigned long long* ctr = a.ws_done + (size_t)b * a.n_kv + j;
-  const unsigned long long before = split_arrive(ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
-  if (split_complete(ctr, before, 1, a.S)) {
-    if (tid < kSplitBitWords)
-      __hip_atomic_store(a.ws_bits + ((size_t)b * a.n_kv + j) * kSplitBitWords + tid, 0ull, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    if (a.out != nullptr)
-      combine_rows<float, HD, NT>(a.ws_acc, a.ws_ml, static_cast<float*>(a.out), (size_t)b * a.n_q + (size_t)j * g, g, a.S,
-                                  reinterpret_cast<float*>(lds + AL.cmb));
+    combine_rows<float, HD, NT>(a.ws_acc, a.ws_ml, static_cast<float*>(a.out), out0, g, a.S,
+                                reinterpret_cast<float*>(lds + AL.cmb));
   }
 }
 
@@ -1647,20 +1640,20 @@ static hipError_t fused_t(const FusedArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The fp32 roles take calls of at most kF32SplitMaxTiles tiles (and as many
-// chunks per sequence as there are completion bits); larger ones fill the chip
-// with tiles of both halves.
+// A partials-only call (out == nullptr) leaves the split counters alone, so it has
+// no place for the roles' flags.
 template <int HD>
 static hipError_t fused_f32_t(const FusedArgs& a, hipStream_t st) {
-  if (a.n_rec < 1 || a.n_rec > kSplitMaxChunks || (long long)a.n_kv * a.B * a.n_rec > kF32SplitMaxTiles)
-    return fused_t<float, HD, 0>(a, st);
+  if (a.out == nullptr || !f32_roles((long long)a.n_kv * a.B, a.n_rec)) return fused_t<float, HD, 0>(a, st);
   const size_t bytes = fused_lds_bytes<float>(a.n_q / a.n_kv, HD, kMtF32) + gamma_lds_bytes(a.d);
   static std::atomic<size_t> done{0};
   auto k = f32_split_kernel<HD>;
   hipError_t e = ensure_lds(k, bytes, done);
   if (e != hipSuccess) return e;
-  const int C = a.S + a.n_rec;
-  hipLaunchKernelGGL(k, dim3((unsigned)((long long)a.n_kv * a.B * C)), dim3(kNtTile), bytes, st, a);
+  const long long units = (long long)a.n_kv * a.B;
+  const int pair_slots = 2 * (int)((units * a.n_rec + kXcds - 1) / kXcds);
+  const long long tail_slots = (units * (a.S - a.n_rec) + kXcds - 1) / kXcds;
+  hipLaunchKernelGGL(k, dim3((unsigned)(kXcds * (pair_slots + tail_slots))), dim3(kNtTile), bytes, st, a, pair_slots);
   return hipGetLastError();
 }
 

@@ -54,8 +54,10 @@ struct FusedArgs {
   float eps;
   // split engine: per (b, KV head) kSplitBitWords words of K-role completion
   // bits (zero between calls), and per (b, KV head, chunk) xf floats of the
-  // K role's probabilities [g][kMtSplit + fold rows] and (max, sum) [g][2]
+  // K role's probabilities [g][kMtSplit + fold rows] and (max, sum) [g][2].
+  // fp32 roles: flag_words words per (b, KV head), 0 with the flags in ws_done (RoleFlag)
   unsigned long long* ws_bits;
+  int flag_words;
   float* xch;
   int xf;
   double rev[kMaxPairs];

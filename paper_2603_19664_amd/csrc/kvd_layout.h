@@ -54,7 +54,13 @@ constexpr int split_xf(int g, int mt) { return (g * (mt + 4) + 2 * g + 3) / 4 * 
 // this many CUs (half the chip): sliding-window layers and short contexts at
 // small batch, where each workgroup's K-loop over d_model sets the time.
 constexpr long long kSplit64MaxTiles = 128;
-constexpr int kF32SplitMaxTiles = 128;  // the fp32 roles: twice as many workgroups, at most one per CU
+// The fp32 roles take calls of at most kF32SplitMaxTiles tiles (twice as many
+// workgroups, at most one per CU); larger ones fill the chip with tiles of both
+// halves.
+constexpr int kF32SplitMaxTiles = 128;
+constexpr bool f32_roles(long long pairs, int n_rec) { return n_rec >= 1 && pairs * n_rec <= kF32SplitMaxTiles; }
+// Chunks whose completion flags fit the high half of their split counter.
+constexpr int kRoleCtrChunks = 32;
 constexpr int split_ld(int hd) { return hd + 8; }
 // Prefill / recompute (kvd_recompute_kv, the block forward's projections) runs
 // on the split engine for bf16 at head_dim 256, and at head_dim 128 when its

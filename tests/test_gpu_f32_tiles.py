@@ -68,3 +68,40 @@ def test_f32_fused_equals_stored_attention(B, T):
         assert torch.equal(_bits(out), _bits(ref))
     n = -(-B * s.n_kv_heads * 8 // 256) * 256 + -(-B * s.n_kv_heads * 32 // 256) * 256
     assert int(torch.count_nonzero(ws[:n])) == 0  # counters and completion words
+
+
+# one KV head x 40 chunks: more than the counter's high half has flags for; a
+# stored tail of 70 rows beside the roles; 240 tiles: both halves in one workgroup
+@pytest.mark.parametrize("B,T,n_q,n_kv,n_tail", [(1, 256, 9, 3, 1), (2, 300, 9, 3, 70), (1, 2560, 3, 1, 1),
+                                                 (3, 2600, 2, 1, 0), (20, 256, 9, 3, 1)])
+def test_f32_workspace_with_only_the_split_counters_zero(B, T, n_q, n_kv, n_tail):
+    # kvd.h asks for zero split counters and nothing else: on a workspace whose other
+    # bytes hold anything (a completion flag set, a count reached) the call gives the
+    # zeroed workspace's bits, the first time and again
+    L = make_layer(C.SMOLLM_FP32, B=B, T=T + n_tail, seed=T, n_q=n_q, n_kv=n_kv, pos0=[5 * b for b in range(B)])
+    s = L.shape
+    K, V = gpu_recompute(L)
+    q = torch.randn((B, n_q, s.head_dim), device="cuda")
+    n = -(-B * n_kv * 8 // 256) * 256
+
+    def call(ws, out):
+        kvd.kvd_fused_recompute_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, K if n_tail else None,
+                                     V if n_tail else None, n_tail, T if n_tail else 0)
+
+    ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, n_tail)
+    ref = torch.empty_like(q)
+    call(ws, ref)
+    for fill in (0xFF, 0x01):
+        ws[n:] = fill
+        for _ in range(2):
+            out = torch.empty_like(q)
+            call(ws, out)
+            assert torch.equal(_bits(out), _bits(ref))
+        assert int(torch.count_nonzero(ws[:n])) == 0
+    # partials only: the counters may hold anything and are not touched
+    ws[:] = 0xFF
+    call(ws, None)
+    assert bool((ws[:n] == 0xFF).all())
+    out = torch.empty_like(q)
+    kvd.kvd_combine(s, B, kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, B, T, n_tail), ws, out)
+    assert torch.equal(_bits(out), _bits(ref))
