@@ -245,7 +245,9 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  * of at most 4 rows joins the tile before it.  kvd_num_splits gives the count;
  * kvd_workspace_bytes covers every engine.
  * The workspace's split counters follow kvd_decode_attn's contract.
- * out == NULL writes only the split-K partials (see kvd_combine).
+ * out == NULL writes only the split-K partials (see kvd_combine); the counters
+ * need not be zero then (the split engine clears them first, the others leave
+ * them alone).
  * Supports both dtypes.                                                       */
 kvd_status kvd_fused_recompute_attn(const kvd_attn_shape* shape, const void* q, const void* h,
                                     int32_t h_ld, const void* gamma, const void* w_k,

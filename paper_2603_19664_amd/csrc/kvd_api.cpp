@@ -235,10 +235,10 @@ size_t ws_ctr_bytes(const kvd_attn_shape* s, int32_t B) {
 size_t ws_done_bytes(const kvd_attn_shape* s, int32_t B) {
   return ws_ctr_bytes(s, B) + kvd::align_up((size_t)B * s->n_kv_heads * kvd::kSplitBitWords * sizeof(uint64_t), 256);
 }
-// Workspace: split counters [B][n_kv] uint64 first, then the split engine's
-// completion words [B][n_kv][kSplitBitWords] (both zero between calls; their
-// place depends on B only, so calls with any key count can share one
-// workspace), then partial accumulators [B][n_q][S][hd] fp32 and partial
+// Workspace: split counters [B][n_kv] uint64 first, padded to 256 bytes (zero
+// between calls; their place depends on B only, so calls with any key count can
+// share one workspace), then room for completion words [B][n_kv][kSplitBitWords]
+// (role_flags), then partial accumulators [B][n_q][S][hd] fp32 and partial
 // (max, sum) [B][n_q][S][2] fp32, then (split engine) the chunks' exchange
 // records [B][n_kv][n_rec][xf] fp32.
 size_t ws_total(const kvd_attn_shape* s, int32_t B, int32_t S) {
@@ -253,17 +253,25 @@ size_t ws_plan_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
   return ws_total(s, B, p.S) + (is_split(p) ? ws_xch_bytes(s, B, p) : 0);
 }
 // Place of the split engines' completion flags for n_rec chunks per sequence
-// (RoleFlag): the split counters themselves, or words in the rest of their
-// 256-byte padded block, which the caller zeroes with them.  Every call of at most
-// kF32SplitMaxTiles chunks has one: more than kRoleCtrChunks chunks then mean at
-// most three (sequence, KV head) pairs.
+// (RoleFlag), in memory that the caller zeroes: words in the second half of the
+// counters' 256-byte padded block where the counters leave it free, else the
+// counters' high halves.  One of the two serves every call that gets these engines
+// by its sizes: with at most kSplit64MaxTiles (kF32SplitMaxTiles) chunks in all,
+// more than kRoleCtrChunks per sequence mean at most three (sequence, KV head)
+// pairs.  Calls that ask for the split engine may fit neither: those use the
+// completion words, cleared by a kernel of their own since the caller need not.
 struct RoleFlags {
   int32_t words;   // per (sequence, KV head); 0: in the counters
   size_t offset;   // of the words, from the workspace's start
+  bool clear;
 };
 RoleFlags role_flags(const kvd_attn_shape* s, int32_t B, int32_t n_rec) {
-  if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0};
-  return RoleFlags{ceil_div(n_rec, 64), (size_t)B * s->n_kv_heads * sizeof(uint64_t)};
+  const int32_t words = ceil_div(n_rec, 64);
+  const int64_t units = (int64_t)B * s->n_kv_heads;
+  if (units * 8 <= (int64_t)kvd::kRoleWordsAt && units * words * 8 <= 256 - (int64_t)kvd::kRoleWordsAt)
+    return RoleFlags{words, kvd::kRoleWordsAt, false};
+  if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0, false};
+  return RoleFlags{words, ws_ctr_bytes(s, B), true};
 }
 float* ws_acc_ptr(const kvd_attn_shape* s, int32_t B, void* ws) {
   return reinterpret_cast<float*>(static_cast<char*>(ws) + ws_done_bytes(s, B));
@@ -683,13 +691,19 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
   a.ws_acc = ws_acc_ptr(shape, B, ws);
   a.ws_ml = ws_ml_ptr(shape, B, S, ws);
   a.ws_done = ws_done_ptr(ws);
-  if (shape->dtype == KVD_F32) {
+  if (split || shape->dtype == KVD_F32) {
     const RoleFlags f = role_flags(shape, B, plan.n_rec);
     a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + f.offset);
     a.flag_words = f.words;
+    // a partials-only call may come with counters that hold anything
+    if (split && out == nullptr)
+      KVD_TRY(device_status(kvd::launch_fill_zero_u64(ws, (int)(ws_ctr_bytes(shape, B) / sizeof(uint64_t)),
+                                                      (hipStream_t)stream), name));
+    if (split && f.clear)
+      KVD_TRY(device_status(kvd::launch_fill_zero_u64(a.ws_bits, f.words * B * shape->n_kv_heads,
+                                                      (hipStream_t)stream), name));
   }
   if (split) {
-    a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + ws_ctr_bytes(shape, B));
     a.xch = reinterpret_cast<float*>(static_cast<char*>(ws) + ws_total(shape, B, S));
     a.xf = kvd::split_xf(shape->n_q_heads / shape->n_kv_heads, plan.mt);
   }
@@ -741,9 +755,9 @@ kvd_status kvd_fused_recompute_attn_noalloc(const kvd_attn_shape* shape, const v
                 B, T_rec, T_tail, need, kvd::kNoAllocScratchBytes);
   void* ws = nullptr;
   KVD_TRY(device_status(kvd::noalloc_scratch(&ws), "kvd_fused_recompute_attn_noalloc scratch lookup"));
-  // the split counters and completion words start at zero: cleared by a fill
-  // kernel (a kernel node under graph capture, never a memset)
-  KVD_TRY(device_status(kvd::launch_fill_zero_u64(ws, (int)(ws_done_bytes(shape, B) / sizeof(uint64_t)),
+  // the split counters start at zero: cleared by a fill kernel (a kernel node under
+  // graph capture, never a memset)
+  KVD_TRY(device_status(kvd::launch_fill_zero_u64(ws, (int)(ws_ctr_bytes(shape, B) / sizeof(uint64_t)),
                                                   (hipStream_t)stream),
                         "kvd_fused_recompute_attn_noalloc counter clear"));
   return fused_launch(shape, q, h, h_ld, gamma, w_k, w_v, pos0, B, T_rec, tail, T_tail, out, ws,

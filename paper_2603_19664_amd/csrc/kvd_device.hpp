@@ -1746,35 +1746,54 @@ __device__ __forceinline__ bool split_complete(unsigned long long* ctr, unsigned
 // The split engines' handshake of a chunk: its K role sets the flag once its
 // probabilities are written, its V role waits for it.  flag_words == 0 (at most
 // kRoleCtrChunks chunks): bit 32 + c of the (b, KV head) split counter; otherwise
-// bit c % 64 of word c / 64 of the flag_words words at ws_bits.  Both roles
-// arrive at the counter (2 n_rec + n_tail arrivals in all), so the last arrival,
-// which clears counter and words, comes after every access to either, also when
-// a wait ran out: the V role then leaves kRoleTimedOut (bit 31) in the counter.
-constexpr unsigned long long kRoleTimedOut = 1ull << 31;
+// bit c % 64 of word c / 64 of the flag_words words at ws_bits.  V roles (and tail
+// tiles) arrive at the counter, K roles do not: a second arrival per chunk on that
+// word cost 0.8 us at 16 chunks and 3.4 at 64.
+constexpr unsigned long long kRoleTimedOut = 1ull << 31;  // in the counter: some V role's wait ran out
 struct RoleFlag {
   unsigned long long* ctr;
-  unsigned long long* word;
-  unsigned long long bit;
-  __device__ __forceinline__ RoleFlag(unsigned long long* ctr_, unsigned long long* bits, int flag_words, size_t unit, int c)
-      : ctr(ctr_ + unit),
-        word(flag_words ? bits + unit * flag_words + (c >> 6) : ctr_ + unit),
-        bit(flag_words ? 1ull << (c & 63) : 1ull << (32 + c)) {}
-  // K role: publish what its threads have stored, and arrive.
-  __device__ __forceinline__ unsigned long long publish(unsigned long long* bcast) const {
-    if (word == ctr) return split_arrive(ctr, 1 + bit, bcast);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's stores are complete
+  unsigned long long* words;
+  int n_words, c;
+  __device__ __forceinline__ RoleFlag(unsigned long long* ctr_, unsigned long long* bits, int flag_words, size_t unit, int c_)
+      : ctr(ctr_ + unit), words(bits + unit * flag_words), n_words(flag_words), c(c_) {}
+  __device__ __forceinline__ unsigned long long* word() const { return n_words ? words + (c >> 6) : ctr; }
+  __device__ __forceinline__ unsigned long long bit() const { return 1ull << (n_words ? c & 63 : 32 + c); }
+  // K role: what its threads have stored is complete, then the flag.
+  __device__ __forceinline__ void publish() const {
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return split_arrive(ctr, 1, bcast);
+    if (threadIdx.x == 0) __hip_atomic_fetch_or(word(), bit(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  static __device__ __forceinline__ bool poll(unsigned long long* w, unsigned long long bits) {
+    for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
+      if ((__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) == bits) return true;
+      __builtin_amdgcn_s_sleep(2);
+    }
+    return false;
   }
   // V role, one thread: bounded wait; false when it ran out.
   __device__ __forceinline__ bool wait() const {
-    for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
-      if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) return true;
-      __builtin_amdgcn_s_sleep(2);
-    }
+    if (poll(word(), bit())) return true;
     __hip_atomic_fetch_or(ctr, kRoleTimedOut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return false;
+  }
+  // True in the workgroup that arrived last (before: the counter before its
+  // arrival).  It clears counter and flags for the next call; if a wait ran out, a
+  // K role may still be on its way, so it waits (bounded) for all n_rec flags first.
+  __device__ __forceinline__ bool complete(unsigned long long before, int n_rec, int S) const {
+    if ((unsigned)(before & (kRoleTimedOut - 1)) + 1 != (unsigned)S) return false;
+    if (threadIdx.x == 0) {
+      if (before & kRoleTimedOut) {
+        if (n_words == 0) poll(ctr, ((1ull << n_rec) - 1) << 32);
+        for (int w = 0; w < n_words; ++w) {
+          const int left = n_rec - 64 * w;
+          poll(words + w, left >= 64 ? ~0ull : (1ull << left) - 1);
+        }
+      }
+      __hip_atomic_store(ctr, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int w = 0; w < n_words; ++w) __hip_atomic_store(words + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return true;
   }
 };
 

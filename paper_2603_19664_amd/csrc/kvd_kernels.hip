@@ -935,10 +935,10 @@ __global__ __launch_bounds__(kNtWide, 1) void fused_pair_kernel(FusedArgs a, int
 // chunk c) two workgroups of split_nt(HD) threads on the split engine: the K
 // role recomputes the chunk's K rows (with RoPE) and takes tasks 1-2 of the
 // tile attention (scores, max, sum, probabilities), which it writes to the
-// chunk's exchange record before setting bit c of the (b, j) completion words;
-// the V role recomputes the V rows, waits for that bit (a bounded wait), reads
-// the record and takes task 3 (P V), then writes the chunk's split-K partial,
-// arrives at the (b, j) counter and, if last, merges.  The K role of a pair is
+// chunk's exchange record before setting the chunk's flag (RoleFlag); the V role
+// recomputes the V rows, waits for the flag (a bounded wait), reads the record
+// and takes task 3 (P V), then writes the chunk's split-K partial, arrives at the
+// (b, j) counter and, if last, merges.  The K role of a pair is
 // the item before its V role, on the same XCD, so it is dispatched no later
 // than the V role that waits for it and depends on nothing itself.  A folded
 // tail (T_tail <= fold rows: the current token) joins the last chunk, its K
@@ -1023,46 +1023,30 @@ __global__ __launch_bounds__(split_nt(HD), 1) void fused_split_kernel(FusedArgs 
   float* S = reinterpret_cast<float*>(lds + AL.s);
   float* ml = reinterpret_cast<float*>(lds + AL.ml);
   float* xrec = a.xch + (((size_t)b * a.n_kv + j) * C + c) * a.xf;
-  unsigned long long* bits = a.ws_bits + ((size_t)b * a.n_kv + j) * kSplitBitWords;
+  const size_t unit = (size_t)b * a.n_kv + j;
+  const RoleFlag flag(a.ws_done, a.ws_bits, a.flag_words, unit, c);
   if (role == 0) {
     attend_scores_mfma<HD, NT, KPL, KLD>(tile, nk, ROWS, g, lds, AL);
     for (int i = tid; i < g * ROWS; i += NT) store_dev(xrec + i, S[i]);
     if (tid < 2 * g) store_dev(xrec + g * ROWS + tid, ml[tid]);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's record stores are complete
-    __syncthreads();
-    if (tid == 0)
-      __hip_atomic_fetch_or(bits + (c >> 6), 1ull << (c & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    flag.publish();
     return;
   }
-  int* flag = reinterpret_cast<int*>(lds + AL.ctr);
-  if (tid == 0) {
-    int ok = 0;
-    for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
-      if ((__hip_atomic_load(bits + (c >> 6), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (c & 63)) & 1ull) {
-        ok = 1;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
-    *flag = ok;
-  }
+  int* seen = reinterpret_cast<int*>(lds + AL.ctr);
+  if (tid == 0) *seen = flag.wait();
   __syncthreads();
-  const bool ok = *flag != 0;
+  const bool ok = *seen != 0;
   for (int i = tid; i < g * ROWS; i += NT) S[i] = load_dev(xrec + i);
   if (tid < 2 * g) ml[tid] = ok ? load_dev(xrec + g * ROWS + tid) : __builtin_nanf("");
   __syncthreads();
   attend_pv_mfma<HD, NT, KLD>(tile, nk, ROWS, g, lds, AL);
   write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<uint16_t>(g));
-  // every V role arrives (also without out): the last one clears the
-  // completion words for the next call
-  unsigned long long* ctr = a.ws_done + (size_t)b * a.n_kv + j;
-  const unsigned long long before = split_arrive(ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
-  if (split_complete(ctr, before, 1, a.S)) {
-    if (tid < kSplitBitWords) __hip_atomic_store(bits + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (a.out != nullptr)
-      combine_rows<uint16_t, HD, NT>(a.ws_acc, a.ws_ml, static_cast<uint16_t*>(a.out),
-                                     (size_t)b * a.n_q + (size_t)j * g, g, a.S, reinterpret_cast<float*>(lds + AL.cmb));
-  }
+  // every V role arrives (also without out): the last one clears the flags for the
+  // next call
+  const unsigned long long before = split_arrive(flag.ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
+  if (flag.complete(before, C, a.S) && a.out != nullptr)
+    combine_rows<uint16_t, HD, NT>(a.ws_acc, a.ws_ml, static_cast<uint16_t*>(a.out),
+                                   (size_t)b * a.n_q + (size_t)j * g, g, a.S, reinterpret_cast<float*>(lds + AL.cmb));
 }
 
 // ------------------------------------------------------------------ fused recompute + attention, fp32 roles
@@ -1072,7 +1056,7 @@ __global__ __launch_bounds__(split_nt(HD), 1) void fused_split_kernel(FusedArgs 
 // (SmolLM2-135M layer at 256 tokens: 12 tiles, 33.8 us per call with both halves
 // in one workgroup, 24.8 with two).  The K role takes the
 // scores and softmax and publishes the probabilities (RoleFlag); the V role waits
-// for them (bounded), takes P V and writes the partial; whoever arrives last
+// for them (bounded), takes P V, writes the partial, arrives and, if last,
 // merges.  The probabilities travel in the chunk's own partial (64 keys <= HD
 // columns), which the V role then overwrites.  Same arithmetic as fused_kernel:
 // bit-identical results.  Grid: pair p (K role, then V role) on XCD p % 8, the
@@ -1100,9 +1084,7 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a, int 
   const int g = a.n_q / a.n_kv;
   const AttnLds AL = attn_lds(PL.end, g, HD, MT);
   float* kv = reinterpret_cast<float*>(lds + PL.kv);
-  unsigned long long* bcast = reinterpret_cast<unsigned long long*>(lds + AL.ctr);
-  unsigned long long* ctr = a.ws_done + (size_t)b * a.n_kv + j;
-  unsigned long long before;
+  const RoleFlag flag(a.ws_done, a.ws_bits, a.flag_words, (size_t)b * a.n_kv + j, ci);
   if (tail) {  // a stored tile of up to 64 rows, as in fused_body
     const int r0 = ci * kTile, nk = min(kTile, a.T_tail - r0);
     load_q<float, HD, NT>(static_cast<const float*>(a.q), b, a.n_q, j, g, reinterpret_cast<float*>(lds + AL.q));
@@ -1113,7 +1095,6 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a, int 
     __syncthreads();
     attend_tile<float, HD, NT, 1>(kv, nk, MT, g, lds, AL);
     write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, a.n_rec + ci, tile_splits<float>(g));
-    before = split_arrive(ctr, 1, bcast);
   } else {
     const int c = ci, role = (int)(slot & 1u);  // 0: K rows, 1: V rows
     const int t0 = c * MT, n = min(MT, a.T_rec - t0);
@@ -1144,27 +1125,23 @@ __global__ __launch_bounds__(kNtTile, 1) void f32_split_kernel(FusedArgs a, int 
     float* S = reinterpret_cast<float*>(lds + AL.s);
     float* ml = reinterpret_cast<float*>(lds + AL.ml);
     const size_t row0 = (size_t)b * a.n_q + (size_t)j * g;
-    const RoleFlag flag(a.ws_done, a.ws_bits, a.flag_words, (size_t)b * a.n_kv + j, c);
     if (role == 0) {
       attend_scores<float, HD, NT, 1, KLD>(kv, n, MT, g, lds, AL);
       for (int i = tid; i < g * MT; i += NT) store_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT, S[i]);
       if (tid < 2 * g) store_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1), ml[tid]);
-      before = flag.publish(bcast);
-    } else {
-      if (tid == 0) flag.wait();
-      __syncthreads();
-      for (int i = tid; i < g * MT; i += NT) S[i] = load_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT);
-      if (tid < 2 * g) ml[tid] = load_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1));
-      __syncthreads();
-      attend_pv<float, HD, NT, KLD>(kv, n, MT, g, lds, AL);
-      write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<float>(g));
-      before = split_arrive(ctr, 1, bcast);
+      flag.publish();
+      return;
     }
+    if (tid == 0) flag.wait();
+    __syncthreads();
+    for (int i = tid; i < g * MT; i += NT) S[i] = load_dev(a.ws_acc + ((row0 + i / MT) * a.S + c) * HD + i % MT);
+    if (tid < 2 * g) ml[tid] = load_dev(a.ws_ml + ((row0 + tid / 2) * a.S + c) * 2 + (tid & 1));
+    __syncthreads();
+    attend_pv<float, HD, NT, KLD>(kv, n, MT, g, lds, AL);
+    write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<float>(g));
   }
-  if (split_complete(ctr, before & ~kRoleTimedOut, 1, n_tail + 2 * a.n_rec)) {
-    if (tid < a.flag_words)
-      __hip_atomic_store(a.ws_bits + ((size_t)b * a.n_kv + j) * a.flag_words + tid, 0ull, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long before = split_arrive(flag.ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
+  if (flag.complete(before, a.n_rec, a.S)) {
     const size_t out0 = (size_t)b * a.n_q + (size_t)j * g;
     if (before & kRoleTimedOut) {  // a late K role may have overwritten its V role's partial
       for (int i = tid; i < g * HD; i += NT) static_cast<float*>(a.out)[out0 * HD + i] = __builtin_nanf("");

@@ -52,10 +52,10 @@ struct FusedArgs {
   void* out;
   int d, n_q, n_kv, B, T_rec, n_rec, S;
   float eps;
-  // split engine: per (b, KV head) kSplitBitWords words of K-role completion
-  // bits (zero between calls), and per (b, KV head, chunk) xf floats of the
-  // K role's probabilities [g][kMtSplit + fold rows] and (max, sum) [g][2].
-  // fp32 roles: flag_words words per (b, KV head), 0 with the flags in ws_done (RoleFlag)
+  // split engine and fp32 roles: the chunks' completion flags, flag_words words per
+  // (b, KV head) at ws_bits (0: in ws_done; RoleFlag); split engine: per (b, KV
+  // head, chunk) xf floats of the K role's probabilities [g][mt + fold rows] and
+  // (max, sum) [g][2]
   unsigned long long* ws_bits;
   int flag_words;
   float* xch;

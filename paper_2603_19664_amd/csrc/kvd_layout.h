@@ -37,10 +37,10 @@ constexpr int kMtSplit = 128;
 // head_dim 256: 8 waves of one 32-row block each (two per SIMD); head_dim 128:
 // 4 waves (the half has 128 rows).
 constexpr int split_nt(int hd) { return hd == 256 ? 512 : 256; }
-// The fused call on the split engine: the V role of chunk c waits for bit c of
-// its (sequence, KV head)'s completion words, which the K role sets once its
-// probabilities are out; the words are cleared by the workgroup that merges
-// the splits.  At most 64 * kSplitBitWords chunks per sequence.
+// The fused call on the split engine: the V role of chunk c waits for the chunk's
+// completion flag, which the K role sets once its probabilities are out; the
+// flags are cleared by the workgroup that arrives last.  At most 64 *
+// kSplitBitWords chunks per sequence.
 constexpr int kSplitBitWords = 4;
 constexpr int kSplitMaxChunks = 64 * kSplitBitWords;
 // Polls of the V role's bounded wait (about 0.1 s); past it the chunk's partial
@@ -59,8 +59,11 @@ constexpr long long kSplit64MaxTiles = 128;
 // halves.
 constexpr int kF32SplitMaxTiles = 128;
 constexpr bool f32_roles(long long pairs, int n_rec) { return n_rec >= 1 && pairs * n_rec <= kF32SplitMaxTiles; }
-// Chunks whose completion flags fit the high half of their split counter.
+// Chunks whose completion flags fit the high half of their split counter, and the
+// place of flag words in the counters' first 256-byte block (a cache line of their
+// own: the waits poll them while arrivals count).
 constexpr int kRoleCtrChunks = 32;
+constexpr size_t kRoleWordsAt = 128;
 constexpr int split_ld(int hd) { return hd + 8; }
 // Prefill / recompute (kvd_recompute_kv, the block forward's projections) runs
 // on the split engine for bf16 at head_dim 256, and at head_dim 128 when its
