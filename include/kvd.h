@@ -236,7 +236,9 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  * attention as sum_t p_t V_t = W_v sum_t p_t hbar_t, so the residuals are read a
  * second time, weighted with the probabilities, and W_v is applied once (three
  * kernels; scores from unrounded keys).  Their scratch lies in the same
- * workspace; they neither read nor write the split counters.
+ * workspace; they neither read nor write the split counters.  Calls whose scratch
+ * outgrows kvd_workspace_bytes, or whose ws is smaller than that (it must always
+ * hold the splits), run on the engines above.
  * With bf16, T_rec >= 1 and T_tail <= 4 (a decode step's current token) the
  * tail joins the last tile's split on every engine: its rows are copied into
  * LDS while that tile is recomputed.  Otherwise the tail adds one split per

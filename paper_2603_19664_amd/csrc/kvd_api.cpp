@@ -533,6 +533,7 @@ kvd_status check_fused_args(const kvd_attn_shape* shape, const void* q, const vo
 // (kvd_workspace_bytes), so no call needs a larger one.
 struct AbsorbPlan {
   int32_t tile, Tp, S, n_tail, n_done;
+  size_t limit;  // the least workspace that gets this path
   size_t scores, rinv, u, uh, uml, tacc, tml, done, end;  // byte offsets from the workspace's start
 };
 
@@ -574,7 +575,7 @@ void absorb_layout(const kvd_attn_shape* s, int32_t B, int32_t S, AbsorbPlan* p)
 // 2 KV heads, 12 query heads) the second read weighs as much as the saved GEMM:
 // 241.8 us tiled against 243.7 at B = 8 x 16384 tokens, 68.9 against 74.0 at
 // B = 8 x 4096.
-bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_tail, size_t ws_bytes, AbsorbPlan* p) {
+bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_tail, AbsorbPlan* p) {
   if (g_fused_tokens.load(std::memory_order_relaxed) != 0 || s->dtype != KVD_BF16 || s->head_dim != 256) return false;
   if (s->n_q_heads > 16 || s->d_model < kvd::kAbsorbMinD) return false;
   if ((int64_t)s->n_kv_heads * B * ceil_div(T_rec, 64) < kvd::kAbsorbMinTiles) return false;
@@ -599,14 +600,16 @@ bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_ta
   const int64_t slices = ceil_div(s->d_model, kvd::kAbsorbCols);
   if (slices * B * kvd::kAbsorbMaxRanges + (int64_t)p->n_tail * s->n_kv_heads * B > INT32_MAX) return false;
   // ranges of a sequence: enough for about kAbsorbMinWgs workgroups, each at least
-  // 256 tokens, as far as the scratch allows (and the static scratch, so that the
-  // call without a workspace runs the same kernels)
-  const size_t limit = std::min({ws_bytes, fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes});
+  // 256 tokens, as far as the scratch fits the workspace that kvd_workspace_bytes
+  // asks for (whatever larger one the caller brings: the same call gives the same
+  // bits) and the static scratch (so that the call without a workspace runs the
+  // same kernels)
+  p->limit = std::min(fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes);
   const int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
   for (int32_t S = want; S >= 1; --S) {
     if (S > 1 && T_rec / S < 256) continue;
     absorb_layout(s, B, S, p);
-    if (p->end <= limit) return true;
+    if (p->end <= p->limit) return true;
   }
   return false;
 }
@@ -617,9 +620,18 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
                         const void* w_k, const void* w_v, const int32_t* pos0, int32_t B, int32_t T_rec,
                         const kvd_kv_view* tail, int32_t T_tail, void* out, void* ws, size_t ws_bytes,
                         const kvd_kv_view* kv_debug, void* stream, const char* name) {
+  const FusedPlan plan = fused_plan(shape, B, T_rec, T_tail);
+  const int32_t S = plan.S;
+  // one workgroup per (KV head, sequence, split), indexed in 32 bits
+  if ((int64_t)shape->n_kv_heads * B * S > INT32_MAX - 8)
+    return fail(KVD_ERR_SHAPE, "%s: n_kv_heads * B * splits = %lld workgroups is too many", name,
+                (long long)shape->n_kv_heads * B * S);
+  const bool split = is_split(plan);
+  KVD_TRY(check_ws(shape, B, S, ws, ws_bytes, split ? ws_xch_bytes(shape, B, plan) : 0));
+  // a workspace that holds the tiled engine's splits but not the size
+  // kvd_workspace_bytes gives runs the tiled engine
   AbsorbPlan ap{};
-  if (out != nullptr && kv_debug == nullptr && ws != nullptr && (reinterpret_cast<uintptr_t>(ws) & 255u) == 0 &&
-      absorb_plan(shape, B, T_rec, T_tail, ws_bytes, &ap)) {
+  if (out != nullptr && kv_debug == nullptr && absorb_plan(shape, B, T_rec, T_tail, &ap) && ws_bytes >= ap.limit) {
     char* base = static_cast<char*>(ws);
     kvd::AbsorbArgs a{};
     a.q = q;
@@ -659,14 +671,6 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
     fill_rev(shape, a.rev);
     return device_status(kvd::launch_absorb(a, shape->w_layout, ap.tile, (hipStream_t)stream), name);
   }
-  const FusedPlan plan = fused_plan(shape, B, T_rec, T_tail);
-  const int32_t S = plan.S;
-  // one workgroup per (KV head, sequence, split), indexed in 32 bits
-  if ((int64_t)shape->n_kv_heads * B * S > INT32_MAX - 8)
-    return fail(KVD_ERR_SHAPE, "%s: n_kv_heads * B * splits = %lld workgroups is too many", name,
-                (long long)shape->n_kv_heads * B * S);
-  const bool split = is_split(plan);
-  KVD_TRY(check_ws(shape, B, S, ws, ws_bytes, split ? ws_xch_bytes(shape, B, plan) : 0));
   kvd::FusedArgs a{};
   a.q = q;
   a.h = h;

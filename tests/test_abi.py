@@ -488,6 +488,18 @@ def test_binding_rejects_host_tensors_of_the_right_extents():
     _raises("on the GPU", kvd.kvd_decode_attn, SH, x["q"], x["k"], x["v"], 9, x["q"], x["q"])
 
 
+@pytest.mark.parametrize("kw,B,T", [(dict(), 1, 4096), (dict(), 16, 2560), (dict(d_model=1152, n_q_heads=4, n_kv_heads=1), 1, 16384)])
+def test_fused_workspace_below_the_splits_is_refused(kw, B, T):
+    # large head_dim 256 calls too: a workspace that does not hold the tiled engine's
+    # splits is refused, whichever path the call would take
+    s = shape(**kw)
+    S = lib.kvd_num_splits(ctypes.byref(s), kvd.KVD_OP_FUSED, B, T, 1)
+    need = _ws_bytes(s, B, S)
+    assert need <= lib.kvd_workspace_bytes(ctypes.byref(s), kvd.KVD_OP_FUSED, B, T, 1)
+    for n in (need - 256, need // 2, 4096):
+        assert fused(s, h_ld=T, T_rec=T, B=B, ws_bytes=n) == kvd.KVD_ERR_WORKSPACE
+
+
 def test_noalloc_rejects_work_beyond_its_scratch():
     # 64 sequences of 16384 recomputed keys need ~134 MB of split-K partials, more
     # than the 32 MiB static scratch: refused before any HIP call

@@ -148,22 +148,45 @@ def test_absorbed_window_and_longer_store():
     assert err(f64(out[sel]), ref) < TOL
 
 
-def test_workspace_too_small_for_the_absorbed_scratch():
-    # a workspace that holds only the tiled engine's splits was accepted before and
-    # still is: the call runs on the tiled engine
-    L = _layer(7, 450)
+@pytest.mark.parametrize("B,T,d", [(28, 450, 1024), (1, 4133, 2560), (4, 4096, 1024)])
+def test_workspace_size_and_path(B, T, d):
+    # the documented size and any larger one give the same bits (the ranges of a
+    # sequence do not follow the buffer); a smaller workspace that holds the tiled
+    # engine's splits was accepted before and still is, and runs that engine
+    L = _layer(B, T, d)
     s = L.shape
-    q, (tk, tv), _, _ = gpu_fused(L)
-    S = kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, L.B, L.T, 1)
+    q, (tk, tv), ref, _ = gpu_fused(L)
     up = lambda x: -(-x // 256) * 256  # noqa: E731
-    n = (up(L.B * s.n_kv_heads * 8) + up(L.B * s.n_kv_heads * 32) + up(L.B * s.n_q_heads * S * s.head_dim * 4)
-         + up(L.B * s.n_q_heads * S * 8))
-    out, tiled = torch.empty_like(q), torch.empty_like(q)
-    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
-    kvd.kvd_fused_recompute_attn(s, q, L.h, L.T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, tk, tv, 1)
-    kvd.kvd_set_fused_tokens(64)
-    kvd.kvd_fused_recompute_attn(s, q, L.h, L.T, L.gamma, L.lw_k, L.lw_v, L.pos0, tiled, ws, tk, tv, 1)
-    assert err(f64(out), f64(tiled)) < TOL and _counters(ws, L) == 0
+    S = kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, B, T, 1)
+    doc = kvd.kvd_workspace_bytes(s, kvd.KVD_OP_FUSED, B, T, 1)
+    least = (up(B * s.n_kv_heads * 8) + up(B * s.n_kv_heads * 32) + up(B * s.n_q_heads * S * s.head_dim * 4)
+             + up(B * s.n_q_heads * S * 8))
+    assert least < doc
+    out = {}
+    for n in (least, doc - 256, doc, doc + 256, 4 * doc):
+        ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        out[n] = torch.empty_like(q)
+        kvd.kvd_fused_recompute_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, out[n], ws, tk, tv, 1)
+        assert _counters(ws, L) == 0
+    kvd.kvd_set_fused_tokens(64 if S == -(-T // 64) else 128)
+    assert kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, B, T, 1) == S
+    _, _, tiled, _ = gpu_fused(L, q=q)
+    assert not torch.equal(_bits(ref), _bits(tiled))
+    for n, o in out.items():
+        assert torch.equal(_bits(o), _bits(tiled if n < doc else ref)), n
+
+
+def test_absorbed_scratch_larger_than_the_workspace():
+    # B = 16 x 512 tokens at d 2560: the residual sums alone outgrow the documented
+    # workspace, so the call runs the tiled engine its sizes give
+    L = _layer(16, 512, 2560)
+    s = L.shape
+    q, _, out, _ = gpu_fused(L)
+    S = kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, 16, 512, 1)
+    kvd.kvd_set_fused_tokens(512 // S)
+    assert kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, 16, 512, 1) == S
+    _, _, tiled, _ = gpu_fused(L, q=q)
+    assert torch.equal(_bits(out), _bits(tiled))
 
 
 def test_absorbed_under_capture():
