@@ -258,7 +258,7 @@ def main():
     log(f"[bench] {ms_step:.3f} ms/step (wall {1e3 * wall / K:.3f}); with per-launch events "
         f"{ms_step_events:.3f} ms/step, fused kernel {1e3 * fused_ms:.1f} us/launch")
 
-    flops = acc.fused_flops(B, T, 1, nq, nkv, d, hd)
+    flops = acc.fused_flops(B, T, 1, nq, nkv, d, hd, kvd.kvd_fused_keys_only(s, B, T, 1))
     achieved = flops / (fused_ms * 1e-3) / 1e12
     traffic = None
     if os.path.exists(TRAFFIC_FILE):
@@ -449,7 +449,7 @@ def run_crossover(args, torch, np, kvd, acc, configs, inputs, op_time, log):
             h_us = op_time(hz, iters=5, flush=flush, median=True)
             del Kh, Vh
         kv_bytes = 2 * Kc.numel() * Kc.element_size()
-        fl = acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim)
+        fl = acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim, kvd.kvd_fused_keys_only(s, B, T, 1))
         S_c = kvd.kvd_num_splits(s, kvd.KVD_OP_CACHED_ATTN, B, T + 1)
         cb = acc.cached_bytes(B, T + 1, wl.n_q, wl.n_kv, wl.head_dim, 2, S_c)
         rows.append({"B": B, "fused_us": f_us, "cached_us": c_us, "ratio_fused_over_cached": f_us / c_us,
@@ -882,8 +882,8 @@ def run_workloads(args, torch, np, kvd, acc, configs, inputs, log, turns=(1, 5, 
     ms = _step_timer(torch, lambda: [c() for c in calls], steps=50, warmup=5)
     res["smollm_fp32"] = {"workload": wl.name, "layers": 1, "batch": B, "ctx": T, "dtype": "f32",
                           "us_per_layer": 1e3 * ms, "tok_s": B / (ms * 1e-3),
-                          "note": "the parity config: fp32 on the vector ALUs (no fp32 MFMA path), 12 workgroups "
-                                  "of 64 keys; latency bound"}
+                          "note": "the parity config: fp32 MFMA, the K and the V rows of 12 64-key tiles in a "
+                                  "workgroup each; latency bound"}
     del layers, calls
     torch.cuda.empty_cache()
 
@@ -904,7 +904,8 @@ def run_workloads(args, torch, np, kvd, acc, configs, inputs, log, turns=(1, 5, 
     ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, 1)
     calls = fused_calls(sc, layers, B, T, T, pos0, pos_new, q, out, tail, ws)
     ms = _step_timer(torch, lambda: [c() for c in calls], steps=c4_steps, warmup=2)
-    flops = L * acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim)
+    flops = L * acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim,
+                                  kvd.kvd_fused_keys_only(s, B, T, 1))
     entry = {"workload": wl.name, "layers": L, "batch": B, "ctx": T, "ms_per_step": ms, "tok_s": B / (ms * 1e-3),
              "us_per_layer": 1e3 * ms / L, "fused_path_tflops": flops / (ms * 1e-3) / 1e12,
              "fused_path_mfma_frac": flops / (ms * 1e-3) / 1e12 / MI355X_BF16_PEAK_TFLOPS}
@@ -946,7 +947,8 @@ def run_workloads(args, torch, np, kvd, acc, configs, inputs, log, turns=(1, 5, 
         ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, 1)
         calls = fused_calls(sc, layers, B, T, Tmax, pos0, pos_new, q, out, tail, ws)
         ms = _step_timer(torch, lambda: [c() for c in calls], steps=3, warmup=1)
-        flops = L * acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim)
+        flops = L * acc.fused_flops(B, T, 1, wl.n_q, wl.n_kv, wl.d_model, wl.head_dim,
+                                    kvd.kvd_fused_keys_only(s, B, T, 1))
         rows.append({"turn": k, "ctx": T, "ms_per_step": ms, "tok_s": B / (ms * 1e-3), "us_per_layer": 1e3 * ms / L,
                      "fused_path_tflops": flops / (ms * 1e-3) / 1e12,
                      "fused_path_mfma_frac": flops / (ms * 1e-3) / 1e12 / MI355X_BF16_PEAK_TFLOPS,

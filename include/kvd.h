@@ -403,6 +403,12 @@ size_t kvd_workspace_bytes(const kvd_attn_shape* shape, int32_t op, int32_t B, i
 int32_t kvd_num_splits(const kvd_attn_shape* shape, int32_t op, int32_t B, int32_t T_main,
                        int32_t T_tail);
 
+/* 1 when kvd_fused_recompute_attn with out, without kv_debug and with a workspace
+ * of kvd_workspace_bytes recomputes keys only for these sizes under the current
+ * kvd_set_fused_tokens setting, else 0 (0 on invalid arguments).  Such a call
+ * does not use the splits that kvd_num_splits counts.                          */
+int32_t kvd_fused_keys_only(const kvd_attn_shape* shape, int32_t B, int32_t T_rec, int32_t T_tail);
+
 /* Tuning of the bf16 stored-K/V attention (kvd_decode_attn, kvd_cached_attn):
  * the number of workgroups its split policy aims for over the whole call
  * (B * n_kv_heads * splits; default 256, one per MI355X compute unit;

@@ -45,15 +45,12 @@ def attention_flops(B: int, T: int, n_q: int, head_dim: int) -> int:
     return 4 * B * T * n_q * head_dim
 
 
-def value_absorbed(B: int, T_rec: int, n_q: int, n_kv: int, d: int, head_dim: int) -> bool:
-    """Whether a bf16 kvd_fused_recompute_attn call recomputes keys only (its rule on sizes)."""
-    return head_dim == 256 and n_q <= 16 and d >= 1024 and B * n_kv * -(-T_rec // 64) >= 192
-
-
-def fused_flops(B: int, T_rec: int, T_tail: int, n_q: int, n_kv: int, d: int, head_dim: int) -> int:
+def fused_flops(B: int, T_rec: int, T_tail: int, n_q: int, n_kv: int, d: int, head_dim: int,
+                keys_only: bool = False) -> int:
     """Work a fused recompute + attention call does: Eq. recomp_flops over the recomputed keys plus attention; on
-    the value-absorbed path the keys' half of it, the scores, the weighted residual sums and one W_v product."""
-    if not value_absorbed(B, T_rec, n_q, n_kv, d, head_dim):
+    the keys-only path (kvd_fused_keys_only says which calls take it) the keys' half of it, the scores, the weighted
+    residual sums and one W_v product."""
+    if not keys_only:
         return recompute_flops(B * T_rec, n_kv, d, head_dim) + attention_flops(B, T_rec + T_tail, n_q, head_dim)
     return (recompute_flops(B * T_rec, n_kv, d, head_dim) // 2 + 2 * B * T_rec * n_q * (head_dim + d)
             + 2 * B * n_q * head_dim * d + attention_flops(B, T_tail, n_q, head_dim))

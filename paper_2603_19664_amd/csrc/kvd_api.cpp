@@ -1065,6 +1065,14 @@ int32_t kvd_num_splits(const kvd_attn_shape* shape, int32_t op, int32_t B, int32
   return splits(shape, op, B, T_main, T_tail);
 }
 
+int32_t kvd_fused_keys_only(const kvd_attn_shape* shape, int32_t B, int32_t T_rec, int32_t T_tail) {
+  if (check_shape(shape) != KVD_OK || check_batch(B) != KVD_OK || B == 0 || T_rec < 1 || T_tail < 0 ||
+      check_lds(shape, true) != KVD_OK)
+    return 0;
+  AbsorbPlan p{};
+  return absorb_plan(shape, B, T_rec, T_tail, &p) ? 1 : 0;
+}
+
 int32_t kvd_set_attn_workgroups(int32_t target) {
   if (target <= 0) target = kvd::kSaTargetWgs;
   target = std::min<int32_t>(target, 1 << 22);

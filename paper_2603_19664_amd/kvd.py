@@ -98,6 +98,8 @@ def _load() -> ctypes.CDLL:
     lib.kvd_workspace_bytes.restype = SZ
     lib.kvd_num_splits.argtypes = [S, I32, I32, I32, I32]
     lib.kvd_num_splits.restype = I32
+    lib.kvd_fused_keys_only.argtypes = [S, I32, I32, I32]
+    lib.kvd_fused_keys_only.restype = I32
     lib.kvd_set_attn_workgroups.argtypes = [I32]
     lib.kvd_set_attn_workgroups.restype = I32
     lib.kvd_set_fused_tokens.argtypes = [I32]
@@ -256,6 +258,11 @@ def kvd_workspace_bytes(shape: Shape, op: int, B: int, T_main: int, T_tail: int 
 
 def kvd_num_splits(shape: Shape, op: int, B: int, T_main: int, T_tail: int = 0) -> int:
     return lib.kvd_num_splits(ctypes.byref(shape.c()), op, B, T_main, T_tail)
+
+
+def kvd_fused_keys_only(shape: Shape, B: int, T_rec: int, T_tail: int = 0) -> bool:
+    """Whether a merged kvd_fused_recompute_attn call of these sizes recomputes keys only."""
+    return bool(lib.kvd_fused_keys_only(ctypes.byref(shape.c()), B, T_rec, T_tail))
 
 
 def kvd_set_attn_workgroups(target: int) -> int:

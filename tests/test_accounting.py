@@ -54,3 +54,30 @@ def test_total_memory_limits():
     assert acc.total_memory(T, 0, L, n_kv, hd, d, b) == T * acc.residual_bytes_per_token(d, b)
     # growth rate in T at fixed budget is d*b per token
     assert acc.total_memory(T + 1, 64, L, n_kv, hd, d, b) - acc.total_memory(T, 64, L, n_kv, hd, d, b) == d * b
+
+
+def test_fused_flops_follow_the_path_a_call_takes():
+    kvd = pytest.importorskip("paper_2603_19664_amd.kvd")
+    s = kvd.Shape(2560, 8, 4, 256, 1e-6, 1e4, kvd.KVD_BF16, kvd.KVD_W_PACKED)
+    B, d, hd, n_q, n_kv = 16, 2560, 256, 8, 4
+
+    def flops(T):
+        return acc.fused_flops(B, T, 1, n_q, n_kv, d, hd, kvd.kvd_fused_keys_only(s, B, T, 1))
+
+    full = lambda T: 4 * B * T * n_kv * d * hd + 4 * B * (T + 1) * n_q * hd  # noqa: E731
+    # a conversation's first turn: the residual sums outgrow the workspace, K and V are recomputed
+    assert not kvd.kvd_fused_keys_only(s, B, 256, 1) and flops(256) == full(256)
+    # half way through: keys only
+    assert kvd.kvd_fused_keys_only(s, B, 2560, 1)
+    assert flops(2560) == (2 * B * 2560 * n_kv * d * hd + 2 * B * 2560 * n_q * (hd + d) + 2 * B * n_q * hd * d
+                           + 4 * B * n_q * hd)
+    # other head sizes, dtypes, long stored tails and forced engines recompute values too
+    import dataclasses as dc
+    for other in (dc.replace(s, head_dim=128), dc.replace(s, dtype=kvd.KVD_F32, w_layout=0)):
+        assert not kvd.kvd_fused_keys_only(other, B, 2560, 1)
+    assert not kvd.kvd_fused_keys_only(s, B, 2560, 64 * 200) and not kvd.kvd_fused_keys_only(s, 0, 2560, 1)
+    try:
+        kvd.kvd_set_fused_tokens(64)
+        assert not kvd.kvd_fused_keys_only(s, B, 2560, 1)
+    finally:
+        kvd.kvd_set_fused_tokens(0)
