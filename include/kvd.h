@@ -231,8 +231,9 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  *     the split engine and bit-identical to the tiles (with the same bounded
  *     wait; past it out is NaN).
  * Before these, in automatic mode with out != NULL and no kv_debug: calls with
- * bf16, head_dim 256, at most 16 query heads, d_model >= 1024 and B *
- * n_kv_heads * ceil(T_rec / 64) >= 192 recompute keys only.  Values enter
+ * bf16, head_dim 256, at most 16 query heads, d_model >= 1024, B * n_kv_heads *
+ * ceil(T_rec / 64) >= 192 and a predicted gain (kvd_fused_keys_only: more KV
+ * heads, larger d_model and longer calls) recompute keys only.  Values enter
  * attention as sum_t p_t V_t = W_v sum_t p_t hbar_t, so the residuals are read a
  * second time, weighted with the probabilities, and W_v is applied once (three
  * kernels; scores from unrounded keys).  Their scratch lies in the same

@@ -565,16 +565,46 @@ void absorb_layout(const kvd_attn_shape* s, int32_t B, int32_t S, AbsorbPlan* p)
   p->end = p->done + kvd::align_up((size_t)4 * p->n_done, 256);
 }
 
+// Times (us) of a head_dim 256 call on either path, to about 5%, from 520 sizes
+// measured on both (d_model 1024 .. 5376, 1 .. 16 KV heads, up to 16 query heads,
+// B 1 .. 16, 192 .. 2048 64-token tiles, packed and row-major weights).
+// Tiled engines: whole rounds of 256 tiles, each the K-loop over d_model plus the
+// tile's attention, and one workgroup per (sequence, KV head) that merges its
+// splits.
+double tiled_us(const kvd_attn_shape* s, int32_t B, const FusedPlan& plan) {
+  const int32_t g = s->n_q_heads / s->n_kv_heads, d = s->d_model;
+  const int64_t rounds = ((int64_t)B * s->n_kv_heads * plan.n_rec + 255) / 256;
+  const bool packed = s->w_layout != KVD_W_ROWMAJOR;
+  const double round = plan.engine == kvd::kFusedWide ? 2.9 * g + (packed ? 8 + 0.0238 * d : 5 + 0.0395 * d)
+                                                      : 0.7 * g + (packed ? 10.6 + 0.0137 * d : 3 + 0.0365 * d);
+  return rounds * round + 0.018 * plan.S * g;
+}
+// Values absorbed: the score tiles' rounds (score_us, at d_model 2560), the second
+// read of the residuals at 4.8 TB/s (3.7 with more than 8 query heads, twice the
+// products), less when its workgroups leave CUs idle, and 15 us for two more
+// launches and the W_v product.
+double absorbed_us(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int64_t score_us, int64_t wgs) {
+  const double read = 2e-6 * B * T_rec * s->d_model / (s->n_q_heads <= 8 ? 4.8 : 3.7);
+  return 15 + score_us * (0.15 + s->d_model / 3370.0) +
+         read * (wgs < 256 ? 1 + 0.14 * (256.0 / wgs - 1) : 1.0);
+}
+
 // True and the plan when the call takes the value-absorbed path: automatic mode,
-// bf16 at head_dim 256, at most 16 query heads, d_model >= 1024 (the streamed read
-// costs as much as the value GEMM it replaces where d_model is short), and at
-// least kAbsorbMinTiles 64-token tiles of the call on the tiled engines.
-// Measured on both sides (Gemma-3-4B layer, whole step, packed weights): 128
-// tiles 44.7 us tiled against 47.7, 188 tiles 51.6 against 50.8, 256 tiles 59.8
-// against 54.4, 512 tiles 91 against 75.  At head_dim 128 (Qwen2.5-1.5B shape:
-// 2 KV heads, 12 query heads) the second read weighs as much as the saved GEMM:
-// 241.8 us tiled against 243.7 at B = 8 x 16384 tokens, 68.9 against 74.0 at
-// B = 8 x 4096.
+// bf16 at head_dim 256, at most 16 query heads, within the measured range
+// (kAbsorbMinD, kAbsorbMinTiles), where it is predicted to be faster than the tiled
+// engine by more than the models miss it (4%, 11% with one or two KV heads).  Of the
+// sizes measured it then loses nowhere by more than 3%, and leaves at most 14% (row-
+// major, d 1024, 192 tiles) unused.  The value GEMM it saves grows
+// with the KV heads, the second read does not: with one KV head (packed weights,
+// d 2560, 4 query heads, B = 16 x 4096 tokens) 162 us tiled against 183, with two
+// 151 against 138, with four (B = 16 x 1024) 151 against 113; one KV head of 8 query
+// heads pays (d 2048, B = 16 x 4096: 193 against 138, the tiled engine's
+// attention is most of the difference), and so does one with row-major weights
+// (296 against 246).  Small calls do not carry the extra launches: d 1024, 4 KV
+// heads, 256 tiles 28 us against 32, 1024 tiles 77 against 65; d 2560, 256 tiles
+// 49 against 45.  At head_dim 128 (Qwen2.5-1.5B shape: 2 KV heads, 12 query heads)
+// the second read weighs as much as the saved GEMM: 241.8 us tiled against 243.7
+// at B = 8 x 16384 tokens, 68.9 against 74.0 at B = 8 x 4096.
 bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_tail, AbsorbPlan* p) {
   if (g_fused_tokens.load(std::memory_order_relaxed) != 0 || s->dtype != KVD_BF16 || s->head_dim != 256) return false;
   if (s->n_q_heads > 16 || s->d_model < kvd::kAbsorbMinD) return false;
@@ -606,10 +636,12 @@ bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_ta
   // same kernels)
   p->limit = std::min(fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes);
   const int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
+  const double margin = s->n_kv_heads <= 2 ? 1.11 : 1.04;
+  const double tiled = tiled_us(s, B, fused_plan(s, B, T_rec, T_tail));
   for (int32_t S = want; S >= 1; --S) {
     if (S > 1 && T_rec / S < 256) continue;
     absorb_layout(s, B, S, p);
-    if (p->end <= p->limit) return true;
+    if (p->end <= p->limit) return margin * absorbed_us(s, B, T_rec, best_us, slices * B * S) < tiled;
   }
   return false;
 }

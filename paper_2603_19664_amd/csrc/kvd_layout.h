@@ -411,7 +411,7 @@ constexpr int kAbsorbMaxRanges = 8;
 // tokens take 25, 18, 15, 13.8, 13.4 us with 1..5 ranges of 20 workgroups; B = 8
 // x 3072 (160 workgroups with one range) 32 us with 1 range, 38 with 2.
 constexpr int kAbsorbMinWgs = 160;
-constexpr int kAbsorbMinTiles = 192;
+constexpr int kAbsorbMinTiles = 192;  // 64-token tiles of the call on the tiled engines
 constexpr int kAbsorbMinD = 1024;
 constexpr int kVprojWaves = 16;
 // 64-row tiles of a stored tail (a remainder of at most 4 rows joins the tile before it).

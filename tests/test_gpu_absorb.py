@@ -1,9 +1,9 @@
 """The value-absorbed fused path (kvd_fused_recompute_attn in automatic mode, bf16,
-head_dim 256, d_model >= 1024, at least 192 64-token tiles, a scratch that fits
-the tiled engines' workspace) against the fp64
-oracle and the tiled engines, at the edges of its tiles: ragged token tiles and
-32-token steps, a last half column slice, one and several ranges per sequence,
-packed and split query-head rows, every kind of stored tail, each score tile.
+head_dim 256, sizes that kvd_fused_keys_only names) against the fp64 oracle and the
+tiled engines, at the edges of its tiles: ragged token tiles and 32-token steps, a
+last half column slice, one and several ranges per sequence, packed and split
+query-head rows, one and two passes over a KV head's query heads and over d_model
+(W_v product), every kind of stored tail, each score tile.
 
 Tolerance: as the tiled engines', 2e-2 of the largest value; the 2-norm error
 against the oracle is besides no larger than the tiled engine's (keys and values
@@ -52,15 +52,19 @@ def _counters(ws, L):
 
 @pytest.mark.parametrize("packed", [False, True, "gamma"])
 @pytest.mark.parametrize("B,T,d,n_q,n_kv", [
-    (7, 450, 1024, 8, 4),     # ragged tiles, one range, 2 query heads per KV head
-    (7, 449, 1088, 8, 4),     # a last half column slice, one token past a tile
-    (4, 449, 1024, 16, 8),    # 16 query heads: two-part rows
-    (8, 512, 1024, 9, 3),     # 768 K rows: 256-row tiles only
-    (24, 500, 1024, 5, 1),    # one KV head
-    (1, 3101, 1024, 8, 4),    # several ranges, a ragged last step
-    (3, 1025, 1216, 16, 4)])  # several ranges, 16 query heads, half slice
+    (28, 450, 1024, 8, 4),     # ragged tiles, one range, 2 query heads per KV head
+    (28, 449, 1088, 8, 4),     # a last half column slice, one token past a tile
+    (14, 449, 1024, 16, 8),    # 16 query heads: two-part rows
+    (28, 512, 1024, 9, 3),     # 768 K rows: 256-row tiles only
+    (60, 1000, 1024, 5, 1),    # one KV head
+    (24, 700, 1024, 12, 1),    # its query heads in two passes of the score epilogue
+    (24, 700, 1024, 16, 1),
+    (4, 1700, 3584, 16, 8),    # two passes of the W_v product over d_model
+    (1, 4133, 2560, 8, 4),     # several ranges, a ragged last step
+    (12, 1025, 1216, 16, 4)])  # several ranges, 16 query heads, half slice
 def test_absorbed_vs_oracle(B, T, d, n_q, n_kv, packed):
     L = _layer(B, T, d, n_q, n_kv, packed=packed)
+    assert kvd.kvd_fused_keys_only(L.shape, B, T, 1)
     q, _, out, _ = gpu_fused(L)
     sel = sorted({0, B // 2, B - 1})
     ref = oracle_decode(L, b_sel=sel)
@@ -74,12 +78,15 @@ def test_absorbed_vs_oracle(B, T, d, n_q, n_kv, packed):
     assert err(f64(out), f64(tiled)) < TOL
 
 
-@pytest.mark.parametrize("T_tail,t_cap,t_off", [(0, 1, 0), (1, 1, 0), (4, 7, 5), (5, 9, 2), (64, 64, 63), (68, 100, 60),
-                                                (70, 80, 33), (200, 211, 150)])
-def test_absorbed_stored_tail(T_tail, t_cap, t_off):
+@pytest.mark.parametrize("B,T,d,n_q,n_kv,T_tail,t_cap,t_off", [
+    (28, 450, 1024, 8, 4, *t) for t in [(0, 1, 0), (1, 1, 0), (4, 7, 5), (5, 9, 2), (64, 64, 63), (68, 100, 60),
+                                        (70, 80, 33), (200, 211, 150)]] + [
+    (12, 1025, 1216, 16, 4, 200, 211, 150),   # several ranges per sequence
+    (24, 700, 1024, 16, 1, 90, 90, 77)])      # 16 query heads per KV head
+def test_absorbed_stored_tail(B, T, d, n_q, n_kv, T_tail, t_cap, t_off):
     # a ring of t_cap slots read from slot t_off, wrapping: rows T .. T + T_tail - 1
-    B, T, d = 7, 450, 1024
-    L = _layer(B, T + T_tail, d)
+    L = _layer(B, T + T_tail, d, n_q, n_kv)
+    assert kvd.kvd_fused_keys_only(L.shape, B, T, T_tail)
     s = L.shape
     K, V = gpu_recompute(L)
     rk, rv = empty_kv(L, t_cap)
@@ -101,7 +108,7 @@ def test_absorbed_stored_tail(T_tail, t_cap, t_off):
         return outs[0]
 
     out, tiled = run(0), run(64)
-    sel = [0, 6]
+    sel = [0, B - 1]
     pos = f64(L.pos0)[sel][:, None] + np.arange(T)[None, :]
     ref = O.kv_direct_decode(f64(q)[sel], f64(L.h[sel, :T]), f64(L.gamma), f64(L.w_k), f64(L.w_v), pos,
                              f64(K[sel, :, T:]) if T_tail else None, f64(V[sel, :, T:]) if T_tail else None,
@@ -112,10 +119,12 @@ def test_absorbed_stored_tail(T_tail, t_cap, t_off):
 
 
 @pytest.mark.parametrize("B,T,n_q,n_kv,packed", [(16, 1000, 8, 4, True), (16, 1000, 8, 4, False),
-                                                 (9, 2048, 8, 8, True), (5, 1500, 6, 3, True), (2, 3000, 8, 4, "gamma")])
+                                                 (9, 2048, 8, 8, True), (5, 1500, 6, 3, True), (2, 3000, 8, 4, "gamma"),
+                                                 (18, 448, 8, 4, False), (16, 640, 6, 3, "gamma")])
 def test_absorbed_score_tiles(B, T, n_q, n_kv, packed):
-    # grids on both sides of the score tiles' rule (512 x 64, 256 x 128, 256 x 64), and
-    # the call without a workspace argument
+    # grids on both sides of the score tiles' rule (512 x 64, 256 x 128, 256 x 64; the
+    # last two: 512 x 64 of row-major and 256 x 128 of folded weights), and the call
+    # without a workspace argument
     L = _layer(B, T, 1024, n_q, n_kv, packed=packed)
     s = L.shape
     q, (tk, tv), out, _ = gpu_fused(L)
@@ -132,7 +141,7 @@ def test_absorbed_score_tiles(B, T, n_q, n_kv, packed):
 
 def test_absorbed_window_and_longer_store():
     # a window over a longer checkpoint store (row stride h_ld > T), positions from 0
-    B, T, W = 7, 900, 451
+    B, T, W = 28, 900, 451
     L = _layer(B, T, 1024)
     s = L.shape
     q = torch.empty((B, s.n_q_heads, s.head_dim), dtype=s.torch_dtype, device="cuda")
@@ -142,6 +151,11 @@ def test_absorbed_window_and_longer_store():
     out = torch.empty_like(q)
     ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, W - 1, 1)
     kvd.kvd_fused_window_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, W, out, ws, tk, tv, 1)
+    assert kvd.kvd_fused_keys_only(s, B, W - 1, 1)
+    tiled = torch.empty_like(q)
+    kvd.kvd_set_fused_tokens(64)
+    kvd.kvd_fused_window_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, W, tiled, ws, tk, tv, 1)
+    assert not torch.equal(_bits(out), _bits(tiled))  # the absorbed path ran
     sel = [0, B - 1]
     ref = O.sliding_window_decode(f64(L.h_new[sel]), f64(L.h[sel, :T]), f64(L.gamma), f64(L.w_q), f64(L.w_k),
                                   f64(L.w_v), W, s.n_q_heads, s.n_kv_heads, s.head_dim, s.rms_eps, s.rope_theta)
@@ -190,7 +204,7 @@ def test_absorbed_scratch_larger_than_the_workspace():
 
 
 def test_absorbed_under_capture():
-    L = _layer(1, 3101)
+    L = _layer(1, 4133, 2560)
     s = L.shape
     q, (tk, tv), ref, _ = gpu_fused(L)
     ws = kvd.workspace(s, kvd.KVD_OP_FUSED, 1, L.T, 1)
@@ -205,7 +219,8 @@ def test_absorbed_under_capture():
         assert torch.equal(_bits(out), _bits(ref))
 
 
-@pytest.mark.parametrize("B,T,d,n_q,n_kv", [(1, 3101, 1024, 8, 4), (3, 1025, 1216, 16, 4), (2, 6200, 2560, 8, 2)])
+@pytest.mark.parametrize("B,T,d,n_q,n_kv", [(1, 4133, 2560, 8, 4), (12, 1025, 1216, 16, 4),
+                                              (2, 6200, 2560, 8, 2)])
 def test_workspace_with_only_the_split_counters_zero(B, T, d, n_q, n_kv):
     # kvd.h asks for zero split counters and nothing else: calls of several ranges on
     # a workspace whose other bytes hold anything equal the call on a zeroed one,
