@@ -632,12 +632,14 @@ bool absorb_plan(const kvd_attn_shape* s, int32_t B, int32_t T_rec, int32_t T_ta
   // ranges of a sequence: enough for about kAbsorbMinWgs workgroups, each at least
   // 256 tokens, as far as the scratch fits the workspace that kvd_workspace_bytes
   // asks for (whatever larger one the caller brings: the same call gives the same
-  // bits) and the static scratch (so that the call without a workspace runs the
-  // same kernels)
-  p->limit = std::min(fused_ws_bytes(s, B, T_rec, T_tail), kvd::kNoAllocScratchBytes);
+  // bits) and, where the call without a workspace takes these sizes, the static
+  // scratch (so that it runs the same kernels)
+  const FusedPlan plan = fused_plan(s, B, T_rec, T_tail);
+  p->limit = fused_ws_bytes(s, B, T_rec, T_tail);
+  if (ws_plan_bytes(s, B, plan) <= kvd::kNoAllocScratchBytes) p->limit = std::min(p->limit, kvd::kNoAllocScratchBytes);
   const int32_t want = (int32_t)std::min<int64_t>(ceil_div(kvd::kAbsorbMinWgs, slices * B), kvd::kAbsorbMaxRanges);
   const double margin = s->n_kv_heads <= 2 ? 1.11 : 1.04;
-  const double tiled = tiled_us(s, B, fused_plan(s, B, T_rec, T_tail));
+  const double tiled = tiled_us(s, B, plan);
   for (int32_t S = want; S >= 1; --S) {
     if (S > 1 && T_rec / S < 256) continue;
     absorb_layout(s, B, S, p);

@@ -71,6 +71,8 @@ def test_fused_flops_follow_the_path_a_call_takes():
     assert kvd.kvd_fused_keys_only(s, B, 2560, 1)
     assert flops(2560) == (2 * B * 2560 * n_kv * d * hd + 2 * B * 2560 * n_q * (hd + d) + 2 * B * n_q * hd * d
                            + 4 * B * n_q * hd)
+    # the largest calls too, whose scratch is more than the workspace-less call's 32 MiB
+    assert kvd.kvd_fused_keys_only(s, 64, 14336, 1) and kvd.kvd_fused_keys_only(s, B, 57344, 1)
     # other head sizes, dtypes, long stored tails and forced engines recompute values too
     import dataclasses as dc
     for other in (dc.replace(s, head_dim=128), dc.replace(s, dtype=kvd.KVD_F32, w_layout=0)):

@@ -203,6 +203,33 @@ def test_absorbed_scratch_larger_than_the_workspace():
     assert torch.equal(_bits(out), _bits(tiled))
 
 
+@pytest.mark.parametrize("T,noalloc", [(16000, True), (36000, False)])
+def test_absorbed_beyond_the_static_scratch(T, noalloc):
+    # sizes whose workspace is larger than the static scratch: where the call without
+    # a workspace takes them it gives the same bits, and beyond the path is the same
+    L = _layer(16, T)
+    s = L.shape
+    assert kvd.kvd_workspace_bytes(s, kvd.KVD_OP_FUSED, 16, T, 1) > 32 << 20 and kvd.kvd_fused_keys_only(s, 16, T, 1)
+    q, (tk, tv), out, _ = gpu_fused(L)
+    na = torch.empty_like(out)
+
+    def call():
+        kvd.kvd_fused_recompute_attn_noalloc(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, na, tk, tv, 1)
+
+    if noalloc:
+        call()
+        assert torch.equal(_bits(out), _bits(na))
+    else:
+        with pytest.raises(kvd.KvdError):
+            call()
+    kvd.kvd_set_fused_tokens(128)
+    _, _, tiled, _ = gpu_fused(L, q=q)
+    ref = oracle_decode(L, b_sel=[15])
+    r, rt = _rel(out[15:], ref), _rel(tiled[15:], ref)
+    note(f"    2-norm vs oracle {r:.3e} (tiled {rt:.3e})")
+    assert err(f64(out), f64(tiled)) < TOL and r <= 1.1 * rt and not torch.equal(_bits(out), _bits(tiled))
+
+
 def test_absorbed_under_capture():
     L = _layer(1, 4133, 2560)
     s = L.shape
