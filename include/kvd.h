@@ -124,7 +124,8 @@ typedef struct {
  *   K[b][j][t_off+t] = RoPE(hbar W_k^(j), pos0[b]+t),  V[b][j][t_off+t] = hbar W_v^(j),
  * hbar = RMSNorm(h[b][t]).  This is also the prefill path (the K/V a cache
  * would have stored).  Every producer runs the same arithmetic (one MFMA chain
- * over d_model per output element, one sum-of-squares order), so prefill,
+ * over d_model per output element, two in fp32 at head_dim 64 and 128; one
+ * sum-of-squares order), so prefill,
  * recompute, kvd_project_qkv's K/V and the fused kernel's K/V are bit-identical
  * for the same residual row and position (Prop. reconstruction).  A bf16 call of
  * few rows (at most 512 workgroups of 32 K/V rows x up to 16 tokens, 1024 for
@@ -206,7 +207,9 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  *   T_rec >= 0, T_tail >= 0, T_rec + T_tail >= 1; tail may be NULL iff T_tail == 0.
  *   ws: kvd_workspace_bytes(shape, KVD_OP_FUSED, B, T_rec, T_tail) bytes.
  *   kv_debug: NULL in production.  If not NULL, the recomputed K/V are also
- *   written to it at rows kv_debug->t_off .. +T_rec-1 (for bit-identity checks).
+ *   written to it at rows kv_debug->t_off .. +T_rec-1 (for bit-identity checks),
+ *   and out comes from the engine that computes them: on sizes where the call
+ *   recomputes keys only without kv_debug, the two outputs differ by rounding.
  * Split-K as in kvd_decode_attn, one split per recomputed tile, on one of
  * four engines (see kvd_set_fused_tokens):
  *   - pair (bf16, head_dim 128, an even n_kv_heads, at most 6 query heads per
@@ -388,8 +391,9 @@ size_t kvd_block_workspace_bytes(const kvd_attn_shape* shape, int32_t d_ff, int3
  * with w_s = 2^(m_s - max_s m_s), over the S partial softmax states that a
  * preceding kvd_decode_attn / kvd_cached_attn / kvd_fused_recompute_attn call
  * (with out == NULL) left in ws, in a fixed order (deterministic; the same
- * arithmetic as the merge those calls run themselves when out != NULL).  S is
- * that call's kvd_num_splits.  Lets a caller time or schedule the merge
+ * arithmetic as the merge those calls run themselves when out != NULL, except
+ * where the merged call recomputes keys only, kvd_fused_keys_only: its output
+ * then differs from this one by rounding).  S is that call's kvd_num_splits.  Lets a caller time or schedule the merge
  * separately.                                                                 */
 kvd_status kvd_combine(const kvd_attn_shape* shape, int32_t B, int32_t S, const void* ws,
                        size_t ws_bytes, void* out, void* stream);
@@ -429,9 +433,10 @@ int32_t kvd_set_attn_workgroups(int32_t target);
  * a call can run on it (elsewhere 64), 64 for the 64-token tiles;
  * other values mean 0.  Returns the previous setting.  Process-wide: it
  * changes kvd_num_splits of KVD_OP_FUSED (not kvd_workspace_bytes, which
- * covers every engine).  All engines give K/V bit-identical to
- * kvd_recompute_kv; the attention output differs by rounding only (other
- * split boundaries).                                                         */
+ * covers every engine), and any value but 0 keeps calls off the keys-only path.
+ * All engines give K/V bit-identical to kvd_recompute_kv; the attention output
+ * differs by rounding only (other split boundaries; keys only: no rounding of K,
+ * V and the probabilities to bf16).                                          */
 #define KVD_FUSED_SPLIT (-128)
 #define KVD_FUSED_SPLIT64 (-64)
 #define KVD_FUSED_PAIR (-2)

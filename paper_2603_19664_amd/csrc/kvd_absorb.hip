@@ -5,10 +5,11 @@
 // their probability-weighted sum, and that is one projection of the weighted
 // sum of the normalised residuals.  So the value half of the token GEMM becomes
 // a second, streamed read of the residuals (2 n_q d flop per token instead of
-// 2 n_kv head_dim d) and one small product per call.  Measured on MI355X per
-// fused call (Gemma-3-4B layer shape): B = 16 x 2560 tokens 389 -> 270 us, B = 8
-// x 3072 with 1025 stored rows 229 -> 165 us, B = 1 x 4096 tokens 52 -> 46 us;
-// the two extra launches (about 15 us at B = 1) are why smaller calls stay on the
+// 2 n_kv head_dim d) and one small product per call.  Measured on MI355X, calls
+// back to back, both paths in turn (Gemma-3-4B layer shape, packed weights): B = 16
+// x 2560 tokens with 100 stored rows 387 -> 265 us, B = 8 x 3072 with 1025 stored
+// rows 250 -> 172, B = 1 x 4096 49.3 -> 44.5 (54.8 -> 52.8 with events around each
+// call); the two extra launches (about 15 us) are why smaller calls stay on the
 // tiled engines.
 #include <atomic>
 
@@ -183,7 +184,7 @@ __device__ __forceinline__ void tail_tile(const AbsorbArgs& a, int item, int row
 }
 
 // grid: n_tail * n_kv * B tail tiles, then (columns / 128) * S * B ranges.  A wave
-// takes 32-token steps of its range (step i to wave i % 8): p r as MFMA A rows
+// takes 32-token steps of its range (step i to wave i % kAbsorbWaves): p r as MFMA A rows
 // (16 query heads x 32 tokens, split into two bf16 parts so that 16 bits of
 // mantissa survive; with PACK, at most 8 heads, the low parts are rows 8..15),
 // the residual rows as B: 8 rows x 16 bytes per lane, transposed in registers
@@ -527,25 +528,13 @@ __global__ __launch_bounds__(64 * kVprojWaves, 1) void vproj_kernel(AbsorbArgs a
 
 // ------------------------------------------------------------------ launchers
 
-template <typename K>
-static hipError_t raise_lds(K kernel, size_t bytes, std::atomic<size_t>& done) {
-  if (bytes <= done.load(std::memory_order_acquire)) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)bytes);
-  if (e != hipSuccess) return e;
-  size_t cur = done.load(std::memory_order_relaxed);
-  while (cur < bytes && !done.compare_exchange_weak(cur, bytes, std::memory_order_release)) {
-  }
-  return hipSuccess;
-}
-
 template <class Tile, int HD, int RW, int MT, bool FOLD>
 static hipError_t score_t(const AbsorbArgs& a, hipStream_t st) {
   if ((a.n_kv * HD) % RW != 0) return hipErrorInvalidValue;
   const size_t bytes = score_lds(HD, a.n_q / a.n_kv, RW, MT, a.d).end;
   static std::atomic<size_t> done{0};
   auto k = score_kernel<Tile, HD, RW, MT, FOLD>;
-  hipError_t e = raise_lds(k, bytes, done);
+  hipError_t e = ensure_lds(k, bytes, done);
   if (e != hipSuccess) return e;
   const int n_rg = a.n_kv * HD / RW;
   const XcdMap m = xcd_map((long long)n_rg * a.B * ((a.T + MT - 1) / MT));
@@ -577,7 +566,7 @@ static hipError_t absorb_t(const AbsorbArgs& a, hipStream_t st) {
   const size_t bytes = main_b > tail_b ? main_b : tail_b;
   static std::atomic<size_t> done{0};
   auto k = absorb_kernel<HD, PACK>;
-  hipError_t e = raise_lds(k, bytes, done);
+  hipError_t e = ensure_lds(k, bytes, done);
   if (e != hipSuccess) return e;
   const long long n = (long long)a.n_tail * a.n_kv * a.B +
                       (long long)((a.d + kAbsorbCols - 1) / kAbsorbCols) * a.S * a.B;
@@ -591,7 +580,7 @@ static hipError_t vproj_t(const AbsorbArgs& a, hipStream_t st) {
   const size_t bytes = sizeof(float) * ((size_t)kVprojWaves * 16 * 17 + 16 * (size_t)(1 + a.n_tail));
   static std::atomic<size_t> done{0};
   auto k = vproj_kernel<HD, L != 0>;
-  hipError_t e = raise_lds(k, bytes, done);
+  hipError_t e = ensure_lds(k, bytes, done);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(a.n_kv * HD / 16, (a.B + seqs - 1) / seqs), dim3(64 * kVprojWaves), bytes, st, a, seqs);
   return hipGetLastError();

@@ -1,7 +1,8 @@
 // Kernels and launchers of libkvd (gfx950).
 //
 //   proj_kernel         RMSNorm + projection + RoPE of token tiles (RECOMPUTE_KV /
-//                       prefill; also the fp32 current-token projection).
+//                       prefill).
+//   f32_proj_kernel     the same in fp32, and the fp32 current-token projection.
 //   stream_proj_kernel  bf16 current-token q, K_t, V_t of a decode step (a GEMV
 //                       shape): four waves per 32 weight rows stream them into an
 //                       LDS ring, one runs the MFMA chain; the same per-element
@@ -13,7 +14,7 @@
 //   fused_pair_kernel   the same per (b, pair of KV heads, 128-key chunk) at bf16
 //                       head_dim 128, on the head_dim 256 wave layout.
 //   fused_split_kernel  the same with a chunk's K and V rows recomputed by two
-//                       workgroups (one half each).
+//                       workgroups (one half each); f32_split_kernel in fp32.
 //   proj_split_kernel / proj_wide_kernel  prefill on the split / wide layouts.
 //   stream_attn_kernel  bf16 stored-K/V attention: per (key split, KV head, b) one
 //                       workgroup streams the split's keys in 16-key blocks, loads of
@@ -1500,26 +1501,6 @@ hipError_t noalloc_scratch(void** out) {
 
 // ------------------------------------------------------------------ launchers
 
-template <typename K>
-static hipError_t set_lds(K kernel, size_t bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
-}
-
-// Raise the kernel's dynamic-LDS limit once per process (per kernel and size).
-// `done` is the largest size already set; threads that race here may both set
-// the attribute, which is idempotent, and the atomic keeps the maximum.
-template <typename K>
-static hipError_t ensure_lds(K kernel, size_t bytes, std::atomic<size_t>& done) {
-  if (bytes <= done.load(std::memory_order_acquire)) return hipSuccess;
-  hipError_t e = set_lds(kernel, bytes);
-  if (e != hipSuccess) return e;
-  size_t cur = done.load(std::memory_order_relaxed);
-  while (cur < bytes && !done.compare_exchange_weak(cur, bytes, std::memory_order_release)) {
-  }
-  return hipSuccess;
-}
-
 // Launcher templates take the weight layout L: 0 row-major, 1 packed, 2 packed
 // with gamma folded in (kvd_weight_layout).
 template <int HD, int L>
@@ -1546,13 +1527,16 @@ static hipError_t f32_proj_nt(const ProjArgs& a, int rows, hipStream_t st) {
   return hipGetLastError();
 }
 
-// One wave per workgroup and 16 tokens while that is at most about one wave per
-// SIMD (the current token); else 64 rows x 32 tokens per workgroup.
+// One wave per workgroup and 16 tokens while that is less than one wave per SIMD
+// (the current token); else 64 rows x 32 tokens per workgroup.  One-wave form
+// against the other, us: d 576 (head_dim 64) 768 waves 11.7 / 11.8, 1032 waves
+// 17.9 / 12.0; d 1024 (128) 768 waves 16.4 / 18.3, 1024 waves 21.0 / 18.4; d 2560
+// (256) 512 waves 24.0 / 38.7, 1024 waves 44.7 / 39.7.
 template <int HD>
 static hipError_t f32_proj_t(const ProjArgs& a, int n_units, hipStream_t st) {
   const int rows = 2 * a.n_kv_units * HD + (n_units > a.n_kv_units ? a.n_q * HD : 0);
   const long long waves = (long long)(rows / 16) * (((long long)a.B * a.T + 15) / 16);
-  if (waves <= 1024) return f32_proj_nt<HD, 1, 1, 12>(a, rows, st);
+  if (waves < 1024) return f32_proj_nt<HD, 1, 1, 12>(a, rows, st);
   return f32_proj_nt<HD, 2, 4, 0>(a, rows, st);
 }
 

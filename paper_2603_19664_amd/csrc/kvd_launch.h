@@ -1,12 +1,34 @@
 // Kernel argument blocks and launcher entry points shared by the C ABI layer
-// (kvd_api.cpp) and the kernels (kvd_kernels.hip).  Internal to libkvd.
+// (kvd_api.cpp) and the kernels.  Internal to libkvd.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "kvd_layout.h"
 
 namespace kvd {
+
+template <typename K>
+inline hipError_t set_lds(K kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
+}
+
+// Raise the kernel's dynamic-LDS limit once per process (per kernel and size).
+// `done` is the largest size already set; threads that race here may both set
+// the attribute, which is idempotent, and the atomic keeps the maximum.
+template <typename K>
+inline hipError_t ensure_lds(K kernel, size_t bytes, std::atomic<size_t>& done) {
+  if (bytes <= done.load(std::memory_order_acquire)) return hipSuccess;
+  hipError_t e = set_lds(kernel, bytes);
+  if (e != hipSuccess) return e;
+  size_t cur = done.load(std::memory_order_relaxed);
+  while (cur < bytes && !done.compare_exchange_weak(cur, bytes, std::memory_order_release)) {
+  }
+  return hipSuccess;
+}
 
 // RMSNorm + projection + RoPE of B*T token rows.  grid.y enumerates units:
 // y < n_kv_units -> KV head y (its K rows get RoPE, V rows do not, written to
@@ -68,10 +90,11 @@ struct FusedArgs {
 //   sum_t p_t V_t = W_v sum_t p_t r_t (gamma * h_t),   r_t = 1 / rms(h_t),
 // and only the keys are recomputed per token.  Three launches:
 //   score_kernel   scores of (b, h, t): q_h . K_t (scaled into the log2 domain) and r_t;
-//   absorb_kernel  per (b, range s of the tokens, 128 columns of h): u[b][s][h] =
-//                  sum_t p_t r_t h_t and the range's (max, sum) in uml; the stored
-//                  tail's 64-row tiles attended into (tacc, tml) beside it;
-//   vproj_kernel   out = (W_v (gamma * sum_s w_s u_s) + sum_tail w acc) / sum w l.
+//   absorb_kernel  per (b, range s of the tokens, 128 columns of h): u_s[h] =
+//                  sum_t p_t r_t h_t and the range's (max, sum); the last range of
+//                  a slice merges them into uh = gamma * sum_s w_s u_s and uml; the
+//                  stored tail's 64-row tiles attended into (tacc, tml) beside it;
+//   vproj_kernel   out = (w W_v uh + sum_tail w acc) / sum w l.
 struct AbsorbArgs {
   const void* q;
   const void* h;

@@ -56,7 +56,9 @@ constexpr int split_xf(int g, int mt) { return (g * (mt + 4) + 2 * g + 3) / 4 * 
 constexpr long long kSplit64MaxTiles = 128;
 // The fp32 roles take calls of at most kF32SplitMaxTiles tiles (twice as many
 // workgroups, at most one per CU); larger ones fill the chip with tiles of both
-// halves.
+// halves.  Tiles of both halves against the roles, us: d 576 (head_dim 64) 120
+// tiles 34.1 / 28.5, 192 tiles 34.6 / 41.8; d 1024 (128) 84 tiles 80.0 / 57.7; d
+// 2560 (256) 84 tiles 334 / 197, 160 tiles 333 / 375.
 constexpr int kF32SplitMaxTiles = 128;
 constexpr bool f32_roles(long long pairs, int n_rec) { return n_rec >= 1 && pairs * n_rec <= kF32SplitMaxTiles; }
 // Chunks whose completion flags fit the high half of their split counter, and the
