@@ -41,7 +41,7 @@ sys.path.insert(0, ROOT)
 MI355X_BF16_PEAK_TFLOPS = 2500.0   # dense bf16 MFMA
 MI355X_HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fused_kernel_traffic.json")
-KERNEL_SOURCES = ["kvd_device.hpp", "kvd_kernels.hip", "kvd_layout.h"]
+KERNEL_SOURCES = ["kvd_absorb.hip", "kvd_device.hpp", "kvd_kernels.hip", "kvd_layout.h"]
 
 
 def parse():

@@ -175,8 +175,9 @@ def sweep_traffic(fetch_dir: str, write_dir: str, trace_csv: str, kernel: str, b
 
 def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_kernel: str, copy_bytes: int, workload: str,
             source_hash: str, command: str) -> dict:
-    """Per-launch HBM bytes of `kernel` from a FETCH_SIZE run and a WRITE_SIZE run, each scaled by
-    what the same counter reads for a plain copy of copy_bytes bytes in the same run."""
+    """Per-launch HBM bytes of `kernel` (or, comma-separated, of the kernels one call launches, added) from a
+    FETCH_SIZE run and a WRITE_SIZE run, each scaled by what the same counter reads for a plain copy of copy_bytes
+    bytes in the same run."""
     def values(directory, counter, name):
         v = []
         for p in glob.glob(os.path.join(directory, "**", "*counter_collection.csv"), recursive=True):
@@ -186,20 +187,22 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_kernel: str, copy_
         if not v:
             raise SystemExit(f"no {counter} samples for {name} under {directory}")
         return [x for _, x in sorted(v)]
-    fv = values(fetch_dir, "FETCH_SIZE", kernel)
-    wv = values(write_dir, "WRITE_SIZE", kernel)
-    f_k, nf, w_k, nw = sum(fv) / len(fv), len(fv), sum(wv) / len(wv), len(wv)
     # the calibration copy is the run's first dispatch of the copy kernel (made before anything else)
     f_c = values(fetch_dir, "FETCH_SIZE", copy_kernel)[0]
     w_c = values(write_dir, "WRITE_SIZE", copy_kernel)[0]
     ff = copy_bytes / (f_c * 1024.0)
     fw = copy_bytes / (w_c * 1024.0)
-    fetch = f_k * 1024.0 * ff
-    write = w_k * 1024.0 * fw
+    per = []
+    for k in kernel.split(","):
+        fv, wv = values(fetch_dir, "FETCH_SIZE", k), values(write_dir, "WRITE_SIZE", k)
+        per.append({"kernel": k, "fetch_kib_raw": sum(fv) / len(fv), "write_kib_raw": sum(wv) / len(wv),
+                    "dispatches": [len(fv), len(wv)]})
+    fetch = sum(p["fetch_kib_raw"] for p in per) * 1024.0 * ff
+    write = sum(p["write_kib_raw"] for p in per) * 1024.0 * fw
     return {"workload": workload, "kernel": kernel, "source_hash": source_hash, "bytes_per_launch": fetch + write,
-            "fetch_bytes": fetch, "write_bytes": write, "fetch_kib_raw": f_k, "write_kib_raw": w_k,
+            "fetch_bytes": fetch, "write_bytes": write, "kernels": per,
             "copy_bytes": copy_bytes, "copy_fetch_kib": f_c, "copy_write_kib": w_c, "fetch_scale": ff, "write_scale": fw,
-            "dispatches": [nf, nw], "command": command}
+            "command": command}
 
 
 if __name__ == "__main__":
