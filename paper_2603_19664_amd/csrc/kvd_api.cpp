@@ -252,24 +252,31 @@ size_t ws_xch_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
 size_t ws_plan_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
   return ws_total(s, B, p.S) + (is_split(p) ? ws_xch_bytes(s, B, p) : 0);
 }
-// Place of the split engines' completion flags for n_rec chunks per sequence
-// (RoleFlag), in memory that the caller zeroes: words in the second half of the
-// counters' 256-byte padded block where the counters leave it free, else the
-// counters' high halves.  One of the two serves every call that gets these engines
-// by its sizes: with at most kSplit64MaxTiles (kF32SplitMaxTiles) chunks in all,
-// more than kRoleCtrChunks per sequence mean at most three (sequence, KV head)
-// pairs.  Calls that ask for the split engine may fit neither: those use the
-// completion words, cleared by a kernel of their own since the caller need not.
+// Place of the completion flags for n_rec chunks per sequence (RoleFlag).  They have
+// to lie in memory that the caller zeroes or the call clears: a stale flag would let
+// a V role read probabilities that are not written.
+//   split engine: words in the second half of the counters' 256-byte padded block
+//     where the counters leave it free.  With three or four (sequence, KV head)
+//     pairs each has 32 bytes of its own (2048 tokens of the Gemma-3-4B layer: 36.7
+//     us with 8 bytes each, 36.1 with 32; with two pairs 8 bytes are as good).
+//   otherwise the counters' high halves, up to kRoleCtrChunks chunks.
+//   otherwise the completion words, cleared by a kernel of their own.  No call that
+//     gets the split engine by its sizes comes here: with at most kSplit64MaxTiles
+//     chunks in all, more than kRoleCtrChunks per sequence mean at most three pairs.
+//     fp32 calls do (33 to 128 chunks of one sequence; 29.3 us with the clear, 33.6
+//     on whole tiles): the padding was never theirs.
 struct RoleFlags {
   int32_t words;   // per (sequence, KV head); 0: in the counters
   size_t offset;   // of the words, from the workspace's start
   bool clear;
 };
 RoleFlags role_flags(const kvd_attn_shape* s, int32_t B, int32_t n_rec) {
-  const int32_t words = ceil_div(n_rec, 64);
-  const int64_t units = (int64_t)B * s->n_kv_heads;
-  if (units * 8 <= (int64_t)kvd::kRoleWordsAt && units * words * 8 <= 256 - (int64_t)kvd::kRoleWordsAt)
+  const int64_t units = (int64_t)B * s->n_kv_heads, room = 256 - (int64_t)kvd::kRoleWordsAt;
+  int32_t words = ceil_div(n_rec, 64);
+  if (s->dtype == KVD_BF16 && units * 8 <= (int64_t)kvd::kRoleWordsAt && units * words * 8 <= room) {
+    if (units > 2 && units * kvd::kSplitBitWords * 8 <= room) words = kvd::kSplitBitWords;
     return RoleFlags{words, kvd::kRoleWordsAt, false};
+  }
   if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0, false};
   return RoleFlags{words, ws_ctr_bytes(s, B), true};
 }
@@ -729,7 +736,8 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
   a.ws_acc = ws_acc_ptr(shape, B, ws);
   a.ws_ml = ws_ml_ptr(shape, B, S, ws);
   a.ws_done = ws_done_ptr(ws);
-  if (split || shape->dtype == KVD_F32) {
+  if (split || (shape->dtype == KVD_F32 && out != nullptr &&
+                kvd::f32_roles((long long)B * shape->n_kv_heads, plan.n_rec))) {
     const RoleFlags f = role_flags(shape, B, plan.n_rec);
     a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + f.offset);
     a.flag_words = f.words;
@@ -737,7 +745,7 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
     if (split && out == nullptr)
       KVD_TRY(device_status(kvd::launch_fill_zero_u64(ws, (int)(ws_ctr_bytes(shape, B) / sizeof(uint64_t)),
                                                       (hipStream_t)stream), name));
-    if (split && f.clear)
+    if (f.clear)
       KVD_TRY(device_status(kvd::launch_fill_zero_u64(a.ws_bits, f.words * B * shape->n_kv_heads,
                                                       (hipStream_t)stream), name));
   }

@@ -1785,7 +1785,7 @@ struct RoleFlag {
     if (threadIdx.x == 0) {
       if (before & kRoleTimedOut) {
         if (n_words == 0) poll(ctr, ((1ull << n_rec) - 1) << 32);
-        for (int w = 0; w < n_words; ++w) {
+        for (int w = 0; 64 * w < n_rec && w < n_words; ++w) {
           const int left = n_rec - 64 * w;
           poll(words + w, left >= 64 ? ~0ull : (1ull << left) - 1);
         }

@@ -70,7 +70,7 @@ def test_f32_fused_equals_stored_attention(B, T):
     assert int(torch.count_nonzero(ws[:n])) == 0  # counters and completion words
 
 
-# one KV head x 40 chunks: more than the counter's high half has flags for; a
+# one KV head x 40 and 41 chunks: more than the counter's high half has flags for; a
 # stored tail of 70 rows beside the roles; 240 tiles: both halves in one workgroup
 @pytest.mark.parametrize("B,T,n_q,n_kv,n_tail", [(1, 256, 9, 3, 1), (2, 300, 9, 3, 70), (1, 2560, 3, 1, 1),
                                                  (3, 2600, 2, 1, 0), (20, 256, 9, 3, 1)])
@@ -82,7 +82,7 @@ def test_f32_workspace_with_only_the_split_counters_zero(B, T, n_q, n_kv, n_tail
     s = L.shape
     K, V = gpu_recompute(L)
     q = torch.randn((B, n_q, s.head_dim), device="cuda")
-    n = -(-B * n_kv * 8 // 256) * 256
+    n = B * n_kv * 8  # the counters alone, without their block's padding
 
     def call(ws, out):
         kvd.kvd_fused_recompute_attn(s, q, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, out, ws, K if n_tail else None,
