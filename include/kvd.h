@@ -172,9 +172,9 @@ kvd_status kvd_project_q(const kvd_attn_shape* shape, const void* h_new, const v
  * same kernel (an atomic split counter in the workspace; no spin-waits).
  * ws (256-byte aligned) must hold kvd_workspace_bytes(shape, KVD_OP_DECODE_ATTN,
  * B, T, 0) bytes.  Workspace contract: its first bytes hold split counters
- * ([B][n_kv_heads] uint64, padded to 256 bytes, the padding included) that
- * must be zero before the first call that uses them (allocate the workspace
- * zero-filled once); every call leaves them zero.  The rest of the workspace is overwritten.  Their
+ * ([B][n_kv_heads] uint64, padded to 256 bytes) that must be zero before the
+ * first call that uses them (allocate the workspace zero-filled once); every
+ * call leaves them zero.  The rest of the workspace is overwritten.  Their
  * place depends on B only, so attention calls of any key count and op (decode,
  * cached, fused) with the same B can share one workspace sized for the largest
  * of them, as a decode loop whose context grows does.  Calls sharing one
@@ -251,9 +251,7 @@ kvd_status kvd_cached_attn(const kvd_attn_shape* shape, const void* q, const kvd
  * of at most 4 rows joins the tile before it.  kvd_num_splits gives the count;
  * kvd_workspace_bytes covers every engine.
  * The workspace's split counters follow kvd_decode_attn's contract.
- * out == NULL writes only the split-K partials (see kvd_combine); the counters
- * need not be zero then (the split engine clears them first, the others leave
- * them alone).
+ * out == NULL writes only the split-K partials (see kvd_combine).
  * Supports both dtypes.                                                       */
 kvd_status kvd_fused_recompute_attn(const kvd_attn_shape* shape, const void* q, const void* h,
                                     int32_t h_ld, const void* gamma, const void* w_k,

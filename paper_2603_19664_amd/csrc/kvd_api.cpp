@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -252,33 +253,34 @@ size_t ws_xch_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
 size_t ws_plan_bytes(const kvd_attn_shape* s, int32_t B, const FusedPlan& p) {
   return ws_total(s, B, p.S) + (is_split(p) ? ws_xch_bytes(s, B, p) : 0);
 }
-// Place of the completion flags for n_rec chunks per sequence (RoleFlag).  They have
-// to lie in memory that the caller zeroes or the call clears: a stale flag would let
-// a V role read probabilities that are not written.
-//   split engine: words in the second half of the counters' 256-byte padded block
-//     where the counters leave it free.  With three or four (sequence, KV head)
-//     pairs each has 32 bytes of its own (2048 tokens of the Gemma-3-4B layer: 36.7
-//     us with 8 bytes each, 36.1 with 32; with two pairs 8 bytes are as good).
-//   otherwise the counters' high halves, up to kRoleCtrChunks chunks.
-//   otherwise the completion words, cleared by a kernel of their own.  No call that
-//     gets the split engine by its sizes comes here: with at most kSplit64MaxTiles
-//     chunks in all, more than kRoleCtrChunks per sequence mean at most three pairs.
-//     fp32 calls do (33 to 128 chunks of one sequence; 29.3 us with the clear, 33.6
-//     on whole tiles): the padding was never theirs.
+// Place of the fp32 roles' completion flags for n_rec chunks per sequence
+// (RoleFlag).  They have to lie in memory that the caller zeroes or the call clears: a
+// stale flag would let a V role read probabilities that are not written.  The split
+// counters' high halves, up to kRoleCtrChunks chunks; else the completion words,
+// cleared by a kernel of their own (one sequence of 33 to 128 chunks: 30.9 us with
+// the clear, 33.6 on whole tiles).
 struct RoleFlags {
   int32_t words;   // per (sequence, KV head); 0: in the counters
   size_t offset;   // of the words, from the workspace's start
-  bool clear;
 };
 RoleFlags role_flags(const kvd_attn_shape* s, int32_t B, int32_t n_rec) {
-  const int64_t units = (int64_t)B * s->n_kv_heads, room = 256 - (int64_t)kvd::kRoleWordsAt;
-  int32_t words = ceil_div(n_rec, 64);
-  if (s->dtype == KVD_BF16 && units * 8 <= (int64_t)kvd::kRoleWordsAt && units * words * 8 <= room) {
-    if (units > 2 && units * kvd::kSplitBitWords * 8 <= room) words = kvd::kSplitBitWords;
-    return RoleFlags{words, kvd::kRoleWordsAt, false};
-  }
-  if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0, false};
-  return RoleFlags{words, ws_ctr_bytes(s, B), true};
+  if (n_rec <= kvd::kRoleCtrChunks) return RoleFlags{0, 0};
+  return RoleFlags{ceil_div(n_rec, 64), ws_ctr_bytes(s, B)};
+}
+
+// A flag value for one launch of the split engine.  The workspace may hold anything,
+// and a replayed graph repeats its value (each replay has replaced every flag by
+// then), so it has to differ from what other launches and ordinary data leave: the
+// high 16 bits make a NaN of the (max, sum) slot it sits in, the other 48 are a
+// mixed counter (splitmix64, Steele, Lea and Flood 2014) that starts at a time- and
+// address-dependent value.
+uint64_t next_tag() {
+  static std::atomic<uint64_t> n{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                                 (uint64_t)reinterpret_cast<uintptr_t>(&g_fused_tokens)};
+  uint64_t z = n.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+  return (0xfff8ull << 48) | ((z ^ (z >> 31)) >> 16);
 }
 float* ws_acc_ptr(const kvd_attn_shape* s, int32_t B, void* ws) {
   return reinterpret_cast<float*>(static_cast<char*>(ws) + ws_done_bytes(s, B));
@@ -736,20 +738,16 @@ kvd_status fused_launch(const kvd_attn_shape* shape, const void* q, const void* 
   a.ws_acc = ws_acc_ptr(shape, B, ws);
   a.ws_ml = ws_ml_ptr(shape, B, S, ws);
   a.ws_done = ws_done_ptr(ws);
-  if (split || (shape->dtype == KVD_F32 && out != nullptr &&
-                kvd::f32_roles((long long)B * shape->n_kv_heads, plan.n_rec))) {
+  if (shape->dtype == KVD_F32 && out != nullptr && kvd::f32_roles((long long)B * shape->n_kv_heads, plan.n_rec)) {
     const RoleFlags f = role_flags(shape, B, plan.n_rec);
     a.ws_bits = reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + f.offset);
     a.flag_words = f.words;
-    // a partials-only call may come with counters that hold anything
-    if (split && out == nullptr)
-      KVD_TRY(device_status(kvd::launch_fill_zero_u64(ws, (int)(ws_ctr_bytes(shape, B) / sizeof(uint64_t)),
-                                                      (hipStream_t)stream), name));
-    if (f.clear)
+    if (f.words > 0)
       KVD_TRY(device_status(kvd::launch_fill_zero_u64(a.ws_bits, f.words * B * shape->n_kv_heads,
                                                       (hipStream_t)stream), name));
   }
   if (split) {
+    a.tag = next_tag();
     a.xch = reinterpret_cast<float*>(static_cast<char*>(ws) + ws_total(shape, B, S));
     a.xf = kvd::split_xf(shape->n_q_heads / shape->n_kv_heads, plan.mt);
   }

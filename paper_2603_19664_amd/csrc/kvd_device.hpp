@@ -1717,8 +1717,8 @@ __device__ __forceinline__ void combine_rows(const float* ws_acc, const float* w
 }
 
 // Split-K completion counter of (b, KV head j): one 64-bit word in the
-// workspace whose low 32 bits count the arrivals (the high 32 bits are the split
-// engines' completion flags, RoleFlag; zero on the others).  Every thread first
+// workspace whose low 32 bits count the arrivals (the high 32 bits are the fp32 roles'
+// completion flags, RoleFlag; zero on the others).  Every thread first
 // waits for its own device-scope partial stores to complete; then one thread adds
 // `add` and the value before the add is broadcast to the workgroup.
 // No cache-wide write-back or invalidate is needed, so other workgroups that
@@ -1743,12 +1743,11 @@ __device__ __forceinline__ bool split_complete(unsigned long long* ctr, unsigned
   return last;
 }
 
-// The split engines' handshake of a chunk: its K role sets the flag once its
+// The fp32 roles' handshake of a chunk: its K role sets the flag once its
 // probabilities are written, its V role waits for it.  flag_words == 0 (at most
 // kRoleCtrChunks chunks): bit 32 + c of the (b, KV head) split counter; otherwise
 // bit c % 64 of word c / 64 of the flag_words words at ws_bits.  V roles (and tail
-// tiles) arrive at the counter, K roles do not: a second arrival per chunk on that
-// word cost 0.8 us at 16 chunks and 3.4 at 64.
+// tiles) arrive at the counter, K roles do not.
 constexpr unsigned long long kRoleTimedOut = 1ull << 31;  // in the counter: some V role's wait ran out
 struct RoleFlag {
   unsigned long long* ctr;

@@ -936,10 +936,13 @@ __global__ __launch_bounds__(kNtWide, 1) void fused_pair_kernel(FusedArgs a, int
 // chunk c) two workgroups of split_nt(HD) threads on the split engine: the K
 // role recomputes the chunk's K rows (with RoPE) and takes tasks 1-2 of the
 // tile attention (scores, max, sum, probabilities), which it writes to the
-// chunk's exchange record before setting the chunk's flag (RoleFlag); the V role
-// recomputes the V rows, waits for the flag (a bounded wait), reads the record
-// and takes task 3 (P V), then writes the chunk's split-K partial, arrives at the
-// (b, j) counter and, if last, merges.  The K role of a pair is
+// chunk's exchange record before it sets the chunk's flag; the V role recomputes
+// the V rows, waits for the flag (a bounded wait), reads the record and takes task 3
+// (P V), then writes the chunk's split-K partial, arrives at the (b, j) counter
+// and, if last, merges.  The flag is a 64-bit tag that no other launch has
+// (FusedArgs::tag), stored over whatever the workspace held: no word has to start
+// at a known value and none has to be cleared, and a store per chunk costs less
+// than an atomic OR on a shared word.  The K role of a pair is
 // the item before its V role, on the same XCD, so it is dispatched no later
 // than the V role that waits for it and depends on nothing itself.  A folded
 // tail (T_tail <= fold rows: the current token) joins the last chunk, its K
@@ -1024,17 +1027,31 @@ __global__ __launch_bounds__(split_nt(HD), 1) void fused_split_kernel(FusedArgs 
   float* S = reinterpret_cast<float*>(lds + AL.s);
   float* ml = reinterpret_cast<float*>(lds + AL.ml);
   float* xrec = a.xch + (((size_t)b * a.n_kv + j) * C + c) * a.xf;
-  const size_t unit = (size_t)b * a.n_kv + j;
-  const RoleFlag flag(a.ws_done, a.ws_bits, a.flag_words, unit, c);
+  // the chunk's flag: a.tag in its (max, sum) slot of the group's first head, which
+  // the V role's own partial then replaces
+  unsigned long long* flag = reinterpret_cast<unsigned long long*>(
+      a.ws_ml + (((size_t)b * a.n_q + (size_t)j * g) * a.S + c) * 2);
   if (role == 0) {
     attend_scores_mfma<HD, NT, KPL, KLD>(tile, nk, ROWS, g, lds, AL);
     for (int i = tid; i < g * ROWS; i += NT) store_dev(xrec + i, S[i]);
     if (tid < 2 * g) store_dev(xrec + g * ROWS + tid, ml[tid]);
-    flag.publish();
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this thread's record stores are complete
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(flag, a.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
   int* seen = reinterpret_cast<int*>(lds + AL.ctr);
-  if (tid == 0) *seen = flag.wait();
+  if (tid == 0) {
+    int ok = 0;
+    for (unsigned it = 0; it < kSplitSpinLimit; ++it) {
+      if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.tag) {
+        ok = 1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(2);
+    }
+    *seen = ok;
+  }
   __syncthreads();
   const bool ok = *seen != 0;
   for (int i = tid; i < g * ROWS; i += NT) S[i] = load_dev(xrec + i);
@@ -1042,12 +1059,13 @@ __global__ __launch_bounds__(split_nt(HD), 1) void fused_split_kernel(FusedArgs 
   __syncthreads();
   attend_pv_mfma<HD, NT, KLD>(tile, nk, ROWS, g, lds, AL);
   write_partial<HD, NT>(lds, AL, a.ws_acc, a.ws_ml, b, a.n_q, j, g, a.S, c, tile_splits<uint16_t>(g));
-  // every V role arrives (also without out): the last one clears the flags for the
-  // next call
-  const unsigned long long before = split_arrive(flag.ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
-  if (flag.complete(before, C, a.S) && a.out != nullptr)
-    combine_rows<uint16_t, HD, NT>(a.ws_acc, a.ws_ml, static_cast<uint16_t*>(a.out),
-                                   (size_t)b * a.n_q + (size_t)j * g, g, a.S, reinterpret_cast<float*>(lds + AL.cmb));
+  if (a.out != nullptr) {
+    unsigned long long* ctr = a.ws_done + (size_t)b * a.n_kv + j;
+    const unsigned long long before = split_arrive(ctr, 1, reinterpret_cast<unsigned long long*>(lds + AL.ctr));
+    if (split_complete(ctr, before, 1, a.S))
+      combine_rows<uint16_t, HD, NT>(a.ws_acc, a.ws_ml, static_cast<uint16_t*>(a.out),
+                                     (size_t)b * a.n_q + (size_t)j * g, g, a.S, reinterpret_cast<float*>(lds + AL.cmb));
+  }
 }
 
 // ------------------------------------------------------------------ fused recompute + attention, fp32 roles

@@ -74,12 +74,14 @@ struct FusedArgs {
   void* out;
   int d, n_q, n_kv, B, T_rec, n_rec, S;
   float eps;
-  // split engine and fp32 roles: the chunks' completion flags, flag_words words per
-  // (b, KV head) at ws_bits (0: in ws_done; RoleFlag); split engine: per (b, KV
-  // head, chunk) xf floats of the K role's probabilities [g][mt + fold rows] and
-  // (max, sum) [g][2]
+  // fp32 roles: the chunks' completion flags, flag_words words per (b, KV head) at
+  // ws_bits (0: in ws_done; RoleFlag)
   unsigned long long* ws_bits;
   int flag_words;
+  // split engine: per (b, KV head, chunk) xf floats of the K role's probabilities
+  // [g][mt + fold rows] and (max, sum) [g][2], and the launch's flag value: a NaN as
+  // a (max, sum) pair, 48 of its bits this launch's own
+  unsigned long long tag;
   float* xch;
   int xf;
   double rev[kMaxPairs];

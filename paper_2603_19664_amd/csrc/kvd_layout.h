@@ -38,9 +38,9 @@ constexpr int kMtSplit = 128;
 // 4 waves (the half has 128 rows).
 constexpr int split_nt(int hd) { return hd == 256 ? 512 : 256; }
 // The fused call on the split engine: the V role of chunk c waits for the chunk's
-// completion flag, which the K role sets once its probabilities are out; the
-// flags are cleared by the workgroup that arrives last.  At most 64 *
-// kSplitBitWords chunks per sequence.
+// flag, which the K role sets once its probabilities are out.  At most 64 *
+// kSplitBitWords chunks per sequence (the workspace has room for that many
+// completion bits; the fp32 roles use them).
 constexpr int kSplitBitWords = 4;
 constexpr int kSplitMaxChunks = 64 * kSplitBitWords;
 // Polls of the V role's bounded wait (about 0.1 s); past it the chunk's partial
@@ -61,11 +61,8 @@ constexpr long long kSplit64MaxTiles = 128;
 // 2560 (256) 84 tiles 334 / 197, 160 tiles 333 / 375.
 constexpr int kF32SplitMaxTiles = 128;
 constexpr bool f32_roles(long long pairs, int n_rec) { return n_rec >= 1 && pairs * n_rec <= kF32SplitMaxTiles; }
-// Chunks whose completion flags fit the high half of their split counter, and the
-// place of flag words in the counters' first 256-byte block (a cache line of their
-// own: the waits poll them while arrivals count).
+// Chunks whose completion flags fit the high half of their split counter.
 constexpr int kRoleCtrChunks = 32;
-constexpr size_t kRoleWordsAt = 128;
 constexpr int split_ld(int hd) { return hd + 8; }
 // Prefill / recompute (kvd_recompute_kv, the block forward's projections) runs
 // on the split engine for bf16 at head_dim 256, and at head_dim 128 when its

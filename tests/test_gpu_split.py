@@ -224,21 +224,19 @@ def test_split64_by_policy_on_small_grids():
     check("auto split64 vs 64-token tiles", out, f64(out64))
 
 
-# flags in the counters (16 and 32 chunks), in the counters' padding (64 chunks;
-# 130 and 41 of 128 tokens), in the completion words (32 units x 41 chunks)
-@pytest.mark.parametrize("mode,B,T,hd", [(0, 1, 1000, 256), (kvd.KVD_FUSED_SPLIT64, 2, 2048, 128), (0, 1, 4096, 128),
+@pytest.mark.parametrize("mode,B,T,hd", [(0, 1, 1000, 256), (0, 8, 200, 256), (kvd.KVD_FUSED_SPLIT64, 2, 2048, 128), (0, 1, 4096, 128),
                                          (kvd.KVD_FUSED_SPLIT64, 16, 2600, 128),
                                          (SPLIT, 4, 16640, 128), (SPLIT, 1, 5200, 256)])
 def test_split_workspace_with_only_the_split_counters_zero(mode, B, T, hd):
     # kvd.h asks for zero split counters and nothing else: on a workspace whose other
     # bytes hold anything the call gives the zeroed workspace's bits, the first time
-    # and again; partials-only calls on counters that hold anything give them too
+    # and again; partials-only calls neither need nor touch the counters
     L = _layer(hd, T, seed=230 + T + hd, B=B)
     s = L.shape
     kvd.kvd_set_fused_tokens(mode)
     q, (tk, tv), ref, _ = gpu_fused(L)
     check("vs oracle", ref[B - 1:], oracle_decode(L, b_sel=[B - 1]))
-    n = -(-B * s.n_kv_heads * 8 // 256) * 256
+    n = B * s.n_kv_heads * 8  # the counters alone, without their block's padding
     ws = kvd.workspace(s, kvd.KVD_OP_FUSED, B, T, 1)
 
     def call(out):
@@ -253,6 +251,32 @@ def test_split_workspace_with_only_the_split_counters_zero(mode, B, T, hd):
         assert int(torch.count_nonzero(ws[:n])) == 0
     ws[:] = 0xFF
     call(None)
+    assert bool((ws[:n] == 0xFF).all())
     out = torch.empty_like(q)
     kvd.kvd_combine(s, B, kvd.kvd_num_splits(s, kvd.KVD_OP_FUSED, B, T, 1), ws, out)
     assert torch.equal(_bits(out), _bits(ref))
+
+
+def test_split_replayed_graph_keeps_its_flag_value():
+    # a captured call repeats its flag value on every replay; between them the
+    # workspace serves eager calls of other lengths and inputs
+    L = _layer(256, 1000, seed=260, B=1)
+    s = L.shape
+    q, (tk, tv), ref, _ = gpu_fused(L)
+    ws = kvd.workspace(s, kvd.KVD_OP_FUSED, 1, L.T, 1)
+    out, other = torch.empty_like(q), torch.empty_like(q)
+    q2 = torch.randn_like(q)
+
+    def call(o, qq, T):
+        kvd.kvd_fused_recompute_attn(s, qq, L.h, T, L.gamma, L.lw_k, L.lw_v, L.pos0, o, ws, tk, tv, 1)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(out, q, L.T)
+    for i in range(6):
+        if i % 2:
+            call(other, q2, L.T - 100 * i)
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(_bits(out), _bits(ref)), i
